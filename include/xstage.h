@@ -367,6 +367,8 @@ int xs_fused_ep_layer_noalloc(const xs_ep_layer* L, const xs_pacing* pacing, con
  * calls: C = A B^T with bf16 operands and fp32 accumulation, bf16 output.
  *   a  device bf16 [M][K] (row stride lda elements), b device bf16 [N][K] (row stride ldb;
  *      the weight's output-major layout), c device bf16 [M][N] (row stride ldc).
+ * Products too small to fill the GPU with 256 x 256 tiles are summed over K in parallel parts
+ * (fp32, a fixed order for given M, N, K); a traced call always runs the tiles.
  * Requires N % 256 == 0, K % 64 == 0, strides multiples of 8. */
 int xs_gemm(const void* a, int64_t lda, const void* b, int64_t ldb, void* c, int64_t ldc,
             int32_t M, int32_t N, int32_t K, const xs_trace* trace, void* stream);

@@ -5,6 +5,7 @@
 #include <algorithm>
 
 #include "xs_gemm.hpp"
+#include "xs_gemm_skinny.hpp"
 
 namespace xs {
 
@@ -330,12 +331,77 @@ static xs_trace trace_or_empty(const xs_trace* t) {
   return *t;
 }
 
+// Split-K launches of the plain GEMM (xs_gemm_skinny.hpp). A form of NB x NJ blocks of 16 x 16
+// costs about kSplitFixed + rounds (NB + NJ) 32 K / kSplitRate, its rounds of workgroups over the
+// CUs each streaming its operand panels at the rate of a CU's memory path; the 256 x 256 tiles
+// cost about kTileFixed + rounds K kTilePerK (half-empty tiles, M <= 128, kTilePerKHalf: they wait
+// for loads rather than for MFMAs). The cheapest wins. Measured, tiles -> split (us): 24 x 4096 x
+// 7168 80 -> 11, 256 x 4096 x 7168 120 -> 24, 512 x 8192 x 4096 71 -> 52, 2048 x 2048 x 2048
+// 40 -> 28; 2048 x 4096 x 4096 stays with the tiles (73, against about 105).
+namespace {
+
+constexpr double kSplitFixed = 2.5, kSplitRate = 75e3;                         // us, bytes per us
+constexpr double kTileFixed = 5.0, kTilePerK = 0.0162, kTilePerKHalf = 0.0105;   // us
+
+template <int NB, int NJ, int kDepth>
+void launch_split(const skinny::Args& p, int N, hipStream_t st) {
+  constexpr int kWaves = 4;
+  hipLaunchKernelGGL((skinny::gemm_kernel<NB, NJ, kDepth, kWaves>), dim3(N / (16 * NJ), (p.M + 16 * NB - 1) / (16 * NB)),
+                     dim3(kWaves * 64), 0, st, p);
+}
+
+// Launches C = A B^T split over K if a split form is the cheapest; false: nothing launched.
+bool gemm_split(const void* a, int64_t lda, const void* b, int64_t ldb, void* c, int64_t ldc, int M, int N, int K,
+                hipStream_t st) {
+  // 16-byte pieces of both operands (8-byte ones of C), and 64 rows of either within 2^31 bytes
+  if (((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b)) & 15) || (reinterpret_cast<uintptr_t>(c) & 7) ||
+      lda > (1 << 23) || ldb > (1 << 23))
+    return false;
+  const int cus = xs_host::persistent_grid(0);
+  const int tiles = ((M + kBM - 1) / kBM) * (N / kBN);
+  double best = kTileFixed + static_cast<double>((tiles + cus - 1) / cus) * K * (M <= kBM / 2 ? kTilePerKHalf : kTilePerK);
+  constexpr int forms[6][2] = {{1, 1}, {2, 1}, {2, 2}, {2, 4}, {4, 2}, {4, 4}};
+  int form = -1;
+  int64_t form_wgs = 0;
+  for (int f = 0; f < 6; ++f) {
+    const int rows = 16 * forms[f][0], cols = 16 * forms[f][1];
+    const int64_t wgs = static_cast<int64_t>((M + rows - 1) / rows) * (N / cols);
+    const double cost = kSplitFixed + static_cast<double>((wgs + cus - 1) / cus) * 2 * (rows + cols) * K / kSplitRate;
+    if (cost < best) {
+      best = cost;
+      form = f;
+      form_wgs = wgs;
+    }
+  }
+  const skinny::Args p{static_cast<const char*>(a), lda * 2, static_cast<const char*>(b), ldb * 2,
+                       static_cast<char*>(c), ldc * 2, M, K};
+  switch (form) {
+    case 0: launch_split<1, 1, 4>(p, N, st); return true;
+    case 1: launch_split<2, 1, 3>(p, N, st); return true;
+    case 2: launch_split<2, 2, 2>(p, N, st); return true;
+    case 3: launch_split<2, 4, 2>(p, N, st); return true;
+    case 4: launch_split<4, 2, 2>(p, N, st); return true;
+    case 5:
+      // one piece in flight per wave leaves the LDS to two workgroups per CU, two pieces to one
+      if (form_wgs > cus) launch_split<4, 4, 1>(p, N, st);
+      else launch_split<4, 4, 2>(p, N, st);
+      return true;
+    default: return false;
+  }
+}
+
+}  // namespace
+
 extern "C" int xs_gemm(const void* a, int64_t lda, const void* b, int64_t ldb, void* c,
                        int64_t ldc, int32_t M, int32_t N, int32_t K, const xs_trace* trace,
                        void* stream) {
   if (!a || !b || !c) return XS_EINVAL;
   if (!gemm_shape_ok(lda, ldb, M, N, K) || ldc < N || ldc % 8) return XS_EUNSUPPORTED;
   if (M == 0) return XS_OK;
+  // a trace records the 256 x 256 tiles
+  const xs_trace tr = trace_or_empty(trace);
+  if (!tr.buf && gemm_split(a, lda, b, ldb, c, ldc, M, N, K, static_cast<hipStream_t>(stream)))
+    return xs_host::launch_status();
   WinSet none{};
   none.n = 0;
   ScatterArgs sa{};
@@ -344,7 +410,7 @@ extern "C" int xs_gemm(const void* a, int64_t lda, const void* b, int64_t ldb, v
   hipLaunchKernelGGL(gemm_tiles_kernel<KIND_PLAIN>, dim3(grid), dim3(kThreads), 0,
                      static_cast<hipStream_t>(stream), static_cast<const uint16_t*>(a), lda,
                      static_cast<const uint16_t*>(b), ldb, static_cast<char*>(c), ldc * 2, M, N,
-                     K, sa, none, trace_or_empty(trace));
+                     K, sa, none, tr);
   return xs_host::launch_status();
 }
 

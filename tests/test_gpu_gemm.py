@@ -41,6 +41,25 @@ def test_gemm_ragged_matches_oracle(M, N, K):
     assert_close(c, osc.gemm(a, b), f"gemm {M}x{N}x{K}")
 
 
+# every split-K form and its edges: a single row, ragged row and K-piece counts (fewer pieces than
+# waves, pieces that leave the last round short), strides beyond K, rows after M left alone. The
+# operands are small integers, so fp32 sums are exact in any order and the bits are unique.
+@pytest.mark.parametrize("M,N,K,pad", [(1, 256, 64, 0), (5, 4096, 192, 0), (16, 512, 448, 8), (24, 4096, 1088, 0),
+                                       (33, 8192, 320, 0), (64, 4096, 576, 16), (72, 7168, 256, 0), (127, 2048, 640, 8),
+                                       (200, 4096, 384, 0), (300, 4096, 704, 8), (513, 2048, 64, 0)])
+def test_gemm_split_forms_bitexact(M, N, K, pad):
+    X = xs()
+    a, b = synth.int_valued_bf16(0, 1, (M, K + pad)), synth.int_valued_bf16(0, 2, (N, K + pad))
+    da, db = dev_bits(a), dev_bits(b)
+    c = torch.full((M + 1, N + 8), -1, dtype=torch.int16, device="cuda")
+    X.check(X.xs_gemm(da.data_ptr(), K + pad, db.data_ptr(), K + pad, c.data_ptr(), N + 8, M, N, K, None, _stream()))
+    torch.cuda.synchronize()
+    got = host_bits(c)
+    ref = f64_to_bf16_bits(osc.gemm(a[:, :K], np.ascontiguousarray(b[:, :K].T)))
+    assert np.array_equal(got[:M, :N], ref)
+    assert (got[M:] == 0xFFFF).all() and (got[:, N:] == 0xFFFF).all()
+
+
 def test_gemm_integer_operands_bitexact():
     # |sums| < 2^24: fp32 accumulation is exact in any order, so the rounded bits are unique
     a = synth.int_valued_bf16(0, 1, (384, 320))

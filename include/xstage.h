@@ -443,7 +443,9 @@ int xs_scatter_copy(const void* c, int64_t ldc, int32_t M, int32_t N, const xs_s
  *   O[h][t][:] = sum_u softmax_u(scale * Q[h][t] . K[h][u]) V[h][u]   (full, non-causal)
  * computed as a flash-attention pass: every persistent workgroup takes 128-query output
  * tiles of one head and streams the head's K/V in 64-token tiles (the Q-loop), with an
- * online softmax in fp32 and bf16 probabilities for the second product.
+ * online softmax in fp32 and bf16 probabilities for the second product. Shapes with at most
+ * one such tile per CU run tiles of 32, 64 or 128 queries whose keys are split over the
+ * workgroup's waves (chosen from heads and M alone).
  *   q, k, v  device bf16 [heads][M][head_dim]; head_dim must be 128.
  *   scale    0 = 1 / sqrt(head_dim).
  *   M        multiple of 128, at most 8,388,480 (one head's K or V rows within a 2 GiB
@@ -460,7 +462,8 @@ int xs_scatter_copy(const void* c, int64_t ldc, int32_t M, int32_t N, const xs_s
  *                    waits until they are visible at system scope before its next Q-loop:
  *                    the completion-coupled issuer the paper argues against (Sec. 4.4, Fig. 7),
  *                    kept as the measured counterfactual.
- * max_producers caps the persistent grid (0 = three workgroups per CU). The optional trace
+ * max_producers caps the persistent grid (0 = three workgroups per CU, one where keys are
+ * split). The optional trace (a traced call never splits keys)
  * records one kind-4 record per output tile: rec[1] tile start, rec[2] end of its Q-loop,
  * rec[3] after its stores were issued. q, k, v and o are 16-byte aligned; windows as for the
  * other window calls (16-byte aligned base and row stride, stride >= heads * head_dim * 2,

@@ -33,7 +33,10 @@
 // columns per 8-byte store, either to the local output or, fused, into the destination
 // window of the tile's sequence chunk; the next tile's Q-loop is the drain window of these
 // stores (no extra wait, no dedicated communication wave).
+//
+// Shapes with at most one such tile per CU run attn_split_kernel instead (below).
 #include <algorithm>
+#include <cfloat>
 #include <cmath>
 
 #include "xs_common.hpp"
@@ -316,6 +319,205 @@ __global__ __launch_bounds__(kThreads, 3) void attn_kernel(Args a) {
   }
 }
 
+// Up to one 128-query tile per CU, the kernel above leaves CUs or wave slots idle: a lone
+// workgroup on a CU is one wave per SIMD, which waits out each K/V tile's loads, products and
+// softmax in turn. Here a workgroup of KS groups of QW waves takes 32 QW queries, group g the K/V
+// tiles g, g + KS, ... of BKV keys, and the groups' softmax states are joined once in LDS at the
+// end. Two slots each of K and V per group and one workgroup barrier per step: tile j + 1 is in
+// flight while tile j is multiplied. What bounds the short forms is each workgroup's stream of
+// its head's whole K and V (a CU takes in about 75 B/ns), so they use the most queries per
+// workgroup that still gives every CU one.
+// Measured, 8 heads (us): M = 128 8.1 -> 5.4, 512 16.5 -> 8.8 (<1, 4, 32>); 1152 30.2 -> 16.4, 2048
+// 49 -> 25.6 (<2, 4, 32>); 4096 95 -> 71.5 (<4, 2, 64>). Three groups a phase
+// apart in lock step (K product, softmax, V product) were slower than this: 85 us at 4096.
+constexpr int kPartialBytes = 16 * 1024 + 512;   // one wave's unnormalised O' and (max, sum), in lane order
+
+template <int QW, int KS, int BKV>
+__global__ __launch_bounds__(QW * KS * 64) void attn_split_kernel(Args a) {
+  constexpr int kQ = 32 * QW;                    // queries per output tile
+  constexpr int kTile = BKV * kRowBytes;         // bytes of a K or V tile
+  constexpr int kNB = BKV / 32;                  // 32-key blocks of a tile
+  constexpr int kLd = kTile / 1024 / QW;         // direct loads per tile and wave
+  constexpr int kStage = KS * 4 * kTile, kJoin = KS * QW * kPartialBytes;
+  __shared__ __attribute__((aligned(16))) char lds_raw[kStage > kJoin ? kStage : kJoin];
+  lds_char* const lds = (lds_char*)lds_raw;
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int w = wv % QW, grp = wv / QW;
+  const int up = lane >> 5;
+  const int qtiles = a.M / kQ;
+  const int ntiles = a.heads * qtiles;
+  static_assert(128 % (KS * BKV) == 0, "M is a multiple of 128: every group has the same number of tiles");
+  const int n = a.M / (KS * BKV);                // K/V tiles of each group
+  const int base = grp * 4 * kTile;              // this group's slots: K 0, K 1, V 0, V 1
+  // lane offsets as in the kernel above
+  uint32_t ko[kLd], vo[kLd];
+#pragma unroll
+  for (int i = 0; i < kLd; ++i) {
+    const int r = 4 * (QW * i + w) + (lane >> 4);
+    ko[i] = static_cast<uint32_t>(r * kRowBytes + (((lane & 15) ^ k_swz(r)) << 4));
+    vo[i] = static_cast<uint32_t>(r * kRowBytes + (((lane & 15) ^ v_swz(r)) << 4));
+  }
+  const int krow = lane & 31;
+  uint32_t kofs[8];
+#pragma unroll
+  for (int kk = 0; kk < 8; ++kk)
+    kofs[kk] = static_cast<uint32_t>(base + krow * kRowBytes + (((2 * kk + up) ^ k_swz(krow)) << 4));
+  const int grp16 = lane >> 4, j16 = lane & 15;
+  const int tr_d = 16 * (grp16 & 1) + 4 * (j16 & 3);
+  const int tr_k = 8 * (grp16 >> 1) + (j16 >> 2);
+  uint32_t vofs[4];
+#pragma unroll
+  for (int db = 0; db < 4; ++db) {
+    const int phys_piece = (4 * db + (tr_d >> 3)) ^ v_swz(tr_k);
+    vofs[db] = static_cast<uint32_t>(base + 2 * kTile + tr_k * kRowBytes + (phys_piece << 4) + ((tr_d >> 2) & 1) * 8);
+  }
+
+  for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
+    const int h = t / qtiles, qt = t - h * qtiles;
+    const int64_t hoff = static_cast<int64_t>(h) * a.M * kD;
+    const int qrow = qt * kQ + 32 * w + (lane & 31);
+    const v4i krs = buffer_rsrc(a.k + hoff, a.M * kRowBytes);
+    const v4i vrs = buffer_rsrc(a.v + hoff, a.M * kRowBytes);
+    auto issue = [&](int j) {                    // the group's K/V tile j into slots j % 2
+      lds_char* st = lds + base + (j & 1) * kTile;
+      const int so = (grp + KS * j) * kTile;
+#pragma unroll
+      for (int i = 0; i < kLd; ++i) load_lds16(krs, ko[i], so, st + (QW * i + w) * 1024);
+#pragma unroll
+      for (int i = 0; i < kLd; ++i) load_lds16(vrs, vo[i], so, st + 2 * kTile + (QW * i + w) * 1024);
+    };
+    issue(0);
+    bf16x8 qf[8];
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk)
+      qf[kk] = *reinterpret_cast<const bf16x8*>(a.q + hoff + static_cast<int64_t>(qrow) * kD + 16 * kk + 8 * up);
+    f32x16 oacc[4];
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) oacc[db][e] = 0.f;
+    // the lowest finite value, so that a group whose first keys all score -inf weighs them 0
+    float m = -FLT_MAX, l = 0.f;
+    for (int j = 0; j < n; ++j) {
+      // tile j has landed in every wave's share, and no wave reads tile j - 1's slots any more
+      wait_vm0();
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      if (j + 1 < n) issue(j + 1);
+      lds_char* const ks = lds + (j & 1) * kTile;
+      f32x16 sacc[kNB];
+#pragma unroll
+      for (int b = 0; b < kNB; ++b) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sacc[b][e] = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) {
+          const bf16x8 kf = *(const lds_bf16x8*)(ks + b * 32 * kRowBytes + kofs[kk]);
+          sacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[kk], sacc[b], 0, 0, 0);
+        }
+      }
+      float mx = sacc[0][0];
+#pragma unroll
+      for (int b = 0; b < kNB; ++b)
+#pragma unroll
+        for (int e = (b ? 0 : 1); e < 16; ++e) mx = fmaxf(mx, sacc[b][e]);
+      const float mxs = max_halves(mx) * a.scale_log2e;
+      if (__builtin_amdgcn_ballot_w64(mxs > m + kRescaleSlack)) {
+        const float m_new = fmaxf(m, mxs);
+        const float corr = __builtin_amdgcn_exp2f(m - m_new);
+        l *= corr;
+#pragma unroll
+        for (int db = 0; db < 4; ++db)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) oacc[db][e] *= corr;
+        m = m_new;
+      }
+      uint32_t pk[kNB][8];
+      float rs = 0.f;
+      const bf16x2_v ones = __builtin_bit_cast(bf16x2_v, 0x3F803F80u);
+#pragma unroll
+      for (int b = 0; b < kNB; ++b)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[b][2 * e], a.scale_log2e, -m));
+          const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[b][2 * e + 1], a.scale_log2e, -m));
+          pk[b][e] = pack_bf16x2(p0, p1);
+          rs = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_v, pk[b][e]), ones, rs, false);
+        }
+      l += add_halves(rs);
+      lds_char* const vs = lds + (j & 1) * kTile;
+#pragma unroll
+      for (int s = 0; s < 2 * kNB; ++s) {
+        const int b = s >> 1, o = 4 * (s & 1);
+        const auto x = __builtin_amdgcn_permlane32_swap(pk[b][o], pk[b][o + 2], false, false);
+        const auto y = __builtin_amdgcn_permlane32_swap(pk[b][o + 1], pk[b][o + 3], false, false);
+        const u32x4 pv = {x[0], y[0], x[1], y[1]};
+        const bf16x8 pf = __builtin_bit_cast(bf16x8, pv);
+#pragma unroll
+        for (int db = 0; db < 4; ++db) {
+          const s16x4 r0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vs + (16 * s) * kRowBytes + vofs[db]));
+          const s16x4 r1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vs + (16 * s + 4) * kRowBytes + vofs[db]));
+          const bf16x8 vf = __builtin_bit_cast(bf16x8, __builtin_shufflevector(r0, r1, 0, 1, 2, 3, 4, 5, 6, 7));
+          oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf, oacc[db], 0, 0, 0);
+        }
+      }
+    }
+    // join: every wave's state to LDS, then group g adds up the column blocks [g 4 / KS, ...) of
+    // all groups, rescaled to the largest maximum, and stores them
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    char* const mine = lds_raw + wv * kPartialBytes;
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *reinterpret_cast<f32x4*>(mine + (4 * db + g) * 1024 + lane * 16) =
+            f32x4{oacc[db][4 * g], oacc[db][4 * g + 1], oacc[db][4 * g + 2], oacc[db][4 * g + 3]};
+    *reinterpret_cast<f32x2_t*>(mine + 16 * 1024 + lane * 8) = f32x2_t{m, l};
+    __syncthreads();
+    float gm[KS], gl[KS], top = -FLT_MAX, sum = 0.f;
+#pragma unroll
+    for (int x = 0; x < KS; ++x) {
+      const f32x2_t ml = *reinterpret_cast<const f32x2_t*>(lds_raw + (x * QW + w) * kPartialBytes + 16 * 1024 + lane * 8);
+      gm[x] = ml.x;
+      gl[x] = ml.y;
+      top = fmaxf(top, gm[x]);
+    }
+#pragma unroll
+    for (int x = 0; x < KS; ++x) {
+      gm[x] = __builtin_amdgcn_exp2f(gm[x] - top);
+      sum += gl[x] * gm[x];
+    }
+    const float inv = 1.f / sum;
+    char* dst;
+    if (a.mode != XS_ATTN_LOCAL) {
+      const int g = (qt * kQ) / a.chunk;    // uniform: a tile lies in one sequence chunk
+      dst = a.win.base[g] + static_cast<int64_t>(qrow - g * a.chunk) * a.win.stride[g] +
+            static_cast<int64_t>(h) * kD * 2;
+    } else {
+      dst = reinterpret_cast<char*>(a.o + hoff + static_cast<int64_t>(qrow) * kD);
+    }
+#pragma unroll
+    for (int d = 0; d < 4 / KS; ++d) {
+      const int db = grp * (4 / KS) + d;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int x = 0; x < KS; ++x) {
+          const f32x4 v = *reinterpret_cast<const f32x4*>(lds_raw + (x * QW + w) * kPartialBytes + (4 * db + g) * 1024 + lane * 16);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) s[e] += v[e] * gm[x];
+        }
+        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+        const u32x2 o = {pack_bf16x2(s[0] * inv, s[1] * inv), pack_bf16x2(s[2] * inv, s[3] * inv)};
+        *(__attribute__((address_space(1))) u32x2*)(dst + (32 * db + 8 * g + 4 * up) * 2) = o;
+      }
+    }
+    if (a.mode == XS_ATTN_WINDOWS_COUPLED) __threadfence_system();
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the next tile's loads reuse the LDS
+  }
+}
+
 // Serial post-attention exchange: one thread per 16-byte piece of o.
 __global__ __launch_bounds__(256) void ulysses_copy_kernel(const uint16_t* __restrict__ o, int heads,
                                                            int M, int D, int chunk, WinSet win) {
@@ -383,11 +585,32 @@ extern "C" int xs_attention(const xs_attn* A, int32_t mode, const xs_trace* trac
     a.chunk = A->M / A->W;
     if (a.chunk % attn::kBQ) return XS_EUNSUPPORTED;
   }
-  const int tiles = A->heads * (A->M / attn::kBQ);
-  int grid = A->max_producers > 0 ? A->max_producers : 3 * xs_host::persistent_grid(0);
+  int tiles = A->heads * (A->M / attn::kBQ);
+  // Waves of queries per workgroup (0: the unsplit kernel, 128 queries and three workgroups per
+  // CU): the most that still leaves every CU a workgroup, from the shape alone, so that the
+  // output depends neither on the grid nor on the mode. Up to one 128-query tile per CU the
+  // split forms win clearly (256 tiles: 71.5 against 95 us); from there on the unsplit kernel has
+  // its second and third workgroup (384 tiles: 181 against 188 us, 512: 265 against 275, 768: 588
+  // against 579). A trace records 128-query tiles of the unsplit kernel.
+  const int cus = xs_host::persistent_grid(0);
+  const int form = a.tr.buf || tiles > cus ? 0 : (4 * tiles <= cus ? 1 : (2 * tiles <= cus ? 2 : 4));
+  if (form) tiles *= 4 / form;
+  int grid = A->max_producers > 0 ? A->max_producers : (form ? cus : 3 * cus);
   if (grid > tiles) grid = tiles;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  hipLaunchKernelGGL(attn::attn_kernel, dim3(grid), dim3(attn::kThreads), 0, st, a);
+  switch (form) {
+    case 1:
+      hipLaunchKernelGGL((attn::attn_split_kernel<1, 4, 32>), dim3(grid), dim3(256), 0, st, a);
+      break;
+    case 2:
+      hipLaunchKernelGGL((attn::attn_split_kernel<2, 4, 32>), dim3(grid), dim3(512), 0, st, a);
+      break;
+    case 4:
+      hipLaunchKernelGGL((attn::attn_split_kernel<4, 2, 64>), dim3(grid), dim3(512), 0, st, a);
+      break;
+    default:
+      hipLaunchKernelGGL(attn::attn_kernel, dim3(grid), dim3(attn::kThreads), 0, st, a);
+  }
   if (xs_host::launch_status()) return XS_EHIP;
   if (mode != XS_ATTN_LOCAL) return xs_host::signal_windows(a.win, st);
   return XS_OK;

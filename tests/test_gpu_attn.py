@@ -79,6 +79,33 @@ def test_attention_matches_oracle(heads, M, qstd):
     assert_close(o, ref64, f"attention h={heads} M={M} qstd={qstd}")
 
 
+# the key-split forms at the edges of their ranges (32-, 64- and 128-query tiles; one K/V tile per
+# group, odd numbers of them), each also with a small grid and as windows
+@pytest.mark.parametrize("heads,M", [(1, 128), (1, 384), (8, 1024), (5, 1664), (8, 2048), (8, 2176), (2, 16384)])
+def test_key_split_forms_match_oracle(heads, M):
+    q, k, v = _inputs(heads, M, seed=71 + M, qstd=2.0)
+    o = _local(q, k, v)
+    pick = slice(None) if M <= 2176 else slice(0, M, 61)
+    ref64, _ = oa.attention(q[:, pick], k, v)
+    assert_close(o[:, pick], ref64, f"attention h={heads} M={M}")
+    assert np.array_equal(o, _local(q, k, v, max_producers=7))
+    win, _ = _fused(q, k, v, 1)
+    assert np.array_equal(_windows_as_heads(win, heads), oa.ulysses_scatter(o, 1))
+
+
+def test_keys_scoring_minus_infinity_weigh_nothing():
+    # positive queries, and keys of -inf from token 40 on: whole K/V tiles (and every tile of most
+    # key groups) score -inf, and the output is attention over the first 40 keys
+    heads, M = 2, 512
+    q, k, v = _inputs(heads, M, seed=81)
+    q = q & 0x7FFF
+    q[q == 0] = 0x3F80
+    k[:, 40:] = 0xFF80
+    o = _local(q, k, v)
+    ref64, _ = oa.attention(q, k[:, :40], v[:, :40])
+    assert_close(o, ref64, "attention with -inf keys")
+
+
 def test_explicit_scale_matches_oracle():
     q, k, v = _inputs(2, 256, seed=11)
     o = _local(q, k, v, scale=0.25)

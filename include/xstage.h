@@ -141,13 +141,13 @@ int xs_dispatch_rows(const void* rows, int64_t row_stride, int32_t row_bytes, in
  * dedup = 0 one entry per (token, k) slot. Lifetime protocol: the producer of entry n
  * (numbered per ring in token order, then k slot order) fills slot n mod S only after entry
  * n - S has been copied out and released; the consumer copies an entry into its window rows
- * (slot_row[t][j] of win[d]) and then releases the slot. Workgroups produce their tokens'
- * entries and consume entries, a stalled producer draining the entries it waits on, so the
+ * (slot_row[t][j] of win[d]) and then releases the slot. Half of the launch's waves produce
+ * tokens' entries, the other half consume entries of every ring throughout, so the
  * call completes for any S >= 1. The windows end equal to xs_dispatch's.
- * max_producers: workgroups (0 = one per CU). spin_timeout_us: bound of every wait (0 = 2 s);
+ * max_producers: pairs of workgroups (0 = one pair per CU). spin_timeout_us: bound of every wait (0 = 2 s);
  * on expiry XS_ETIMEOUT goes to dev_status and the kernel exits. workspace: device bytes from
- * xs_dispatch_ring_workspace_bytes(T, k, W, S) (control words and entry numbers; rewritten
- * by every call). stats:
+ * xs_dispatch_ring_workspace_bytes(T, k, W, S) (control words, entry numbers and their bases;
+ * rewritten by every call). stats:
  * optional device int32 [2W]: entries per destination, then productions that found their
  * slot still occupied. Status words as xs_dispatch (XS_ECAPACITY for rows beyond a window,
  * XS_EBADINPUT for bad experts). Argument errors: XS_EINVAL / XS_EUNSUPPORTED /

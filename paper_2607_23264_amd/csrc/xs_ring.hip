@@ -10,24 +10,28 @@
 //   pub[s] = u + 1  entry n = u S + s is written (system-scope release by its producer);
 //   rel[s] = u + 1  it has been copied out (release by its consumer).
 // The producer of entry n waits for rel[n mod S] == n / S (entry n - S released), writes the
-// row and header, then publishes. A consumer claims entries in order from an atomic tail
-// counter, waits for pub == n / S + 1 (acquire), copies the row into every listed window row,
-// then releases the slot.
+// row and header, then publishes. Its consumer sees pub == n / S + 1, copies the row into every
+// listed window row, then releases the slot.
 //
-// Agents are waves: each produces its tokens' entries and consumes entries on its own, with no
-// workgroup barrier in the protocol, so about two thousand entries are in flight at once.
-// Each claim counter sits on a 128-byte line of its own (counters sharing a line serialise
-// every claim of every ring at one L2 atomic unit).
+// Agents are waves, with no workgroup barrier in the protocol: even waves produce their tokens'
+// entries in token order, odd waves consume. A consumer owns every Q-th entry of a ring (or, with
+// fewer consumers than rings, whole rings), so claiming takes no atomic; it looks at several of
+// its entries at once, one per lane, and consumes whichever are published.
 //
-// Progress: a producer waiting for its slot helps: while the tail has not passed n - S it
-// claims and consumes the oldest entries itself, so the entry it waits for is always either
-// being consumed or consumable by it. Those entries belong to earlier tokens, whose producers
-// are behind this one in token order and so never wait on it. An agent that has produced all
-// its entries drains the rings until every entry is consumed. Every wait is bounded: on
-// time-out an agent reports XS_ETIMEOUT and raises an abort word that makes every other wait
-// give up, so the grid always drains. Same-address device-scope atomics are slow on this
-// GPU (measured: ~0.4 us each, serialised, when every entry took one): producers take no
-// atomic, and a draining agent claims eight entries per atomic.
+// Coherence: on this GPU a release that another XCD must observe writes back the L2, and an
+// acquire invalidates it (agent and system scope cost the same, measured). With such fences, even
+// one per 32 entries, the dispatch of 2048 rows of 14 KiB through 256-slot rings took 857 us,
+// without any 150. So no ring byte is left in an L2: rows, headers and flags are stored with the
+// system-scope bits (sc0 sc1: written through to memory), a producer publishes once its stores
+// have completed (vmcnt 0), and consumers load with the same bits, past the L2. Only the window
+// rows, which are read after the kernel, are cached. What bounds wide rings now is memory: every
+// row is written and read once more than by the plain dispatch (575 MB in those 150 us).
+//
+// Progress: every wave is resident. The earliest entry not yet published (in token order) has
+// a producer that waits at most for an earlier entry of its ring, which is published, and whose
+// consumer waits for no particular entry; a producer publishes what it has written before it
+// waits. Every wait is bounded: on time-out an agent reports XS_ETIMEOUT and raises an abort word
+// that makes every other wait give up, so the grid always drains.
 #include <algorithm>
 
 #include "xs_common.hpp"
@@ -38,12 +42,11 @@ namespace ring {
 constexpr int kThreads = 256;         // four waves; every wave is an independent agent
 constexpr int kMaxK = 32;
 constexpr int kLine = 32;             // ints per 128-byte line: one counter per line
-constexpr int kBatch = 8;             // entries a draining agent claims per atomic
-// Rings of at least kWideRing slots drain in batches of kBatchWide: one acquire and one release
-// per batch, and with slots to spare fewer, larger batches pay fewer fences (measured on one
-// source of the DeepSeek-V3 share: 256 slots 5.5 -> 2.4 ms, 4096 slots 0.97 -> 0.85 ms); in small
-// rings a wide batch holds slots the producers are waiting for (16 slots: 19.5 -> 65 ms).
-constexpr int kBatchWide = 32, kWideRing = 256;
+constexpr int kChunk = 64;            // tokens numbered by one wave of the rank kernel
+constexpr int kPieces = 8;            // 16-byte pieces of a row per lane in flight (with 16, 4 % faster,
+                                      // the kernel needs 174 registers: see the launch bounds)
+constexpr int kLook = 8;              // entries a consumer looks at at once
+constexpr int kCoherent = 17;         // buffer cache policy: sc0 | sc1, system scope
 
 struct RingArgs {
   const char* x;               // token rows, x_stride bytes apart
@@ -55,8 +58,9 @@ struct RingArgs {
   WinSet win;                  // dispatch windows
   char* ring[XS_MAX_WINDOWS];  // ring memory per destination: S slots of slot_bytes
   int64_t slot_bytes;          // payload, then 1 + k header ints
-  int* entry_no;               // [T][k] entry number of each (token, k) slot in its ring
-  int* tail;                   // [W] consumer claim counters, one per line
+  int* entry_no;               // [T][k] entry number of each (token, k) slot in its ring, less its
+                               //        chunk's base
+  int* chunk_base;             // [T / kChunk][W] entries of the ring from earlier chunks
   int* total;                  // [W] entries per destination, one per line
   int* abort_word;
   int* pub;                    // [W][S]
@@ -66,97 +70,82 @@ struct RingArgs {
   int64_t timeout_ticks;
 };
 
-// Exclusive prefix sum of v over the block's threads in order (1024 threads, 16 waves): a
-// shuffle scan inside each wave, then each thread adds the totals of the waves before it.
-// `total` receives the block's sum. Two barriers; wsum is 16 ints of LDS.
-__device__ __forceinline__ int block_exclusive_scan(int v, int* wsum, int& total) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  int x = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(x, o);
-    if (lane >= o) x += y;
-  }
-  if (lane == 63) wsum[wv] = x;
-  __syncthreads();
-  int before = 0, all = 0;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int w = wsum[i];
-    before += i < wv ? w : 0;
-    all += w;
-  }
-  total = all;
-  __syncthreads();
-  return before + x - v;
-}
-
-constexpr int kPlanInts = 32768;   // expert indices staged in LDS per round (128 KiB)
-
-// Entry numbers, entries per destination and a clean control block (one workgroup of 1024).
-// Entries of ring d are numbered in token order (and k slot order within a token without
-// dedup): for each destination an exclusive scan over contiguous token chunks, one per thread.
-__global__ __launch_bounds__(1024) void ring_plan_kernel(RingArgs a) {
-  __shared__ int sidx[kPlanInts];
-  __shared__ int wsum[16];
-  __shared__ int base[XS_MAX_WINDOWS];
+// Entry numbers within each chunk of 64 tokens, the chunks' entries per ring, and a clean control
+// block. One wave per chunk, one token per lane: entries of a ring are numbered in token order
+// (and k slot order within a token without dedup), a prefix sum over the lanes by ballots of the
+// counts' bits.
+__global__ __launch_bounds__(kThreads) void ring_rank_kernel(RingArgs a) {
   const int W = a.win.n;
   const int epw = a.E / W;
-  const int tid = threadIdx.x;
-  for (int i = tid; i < W; i += blockDim.x) {
-    a.tail[i * kLine] = 0;
-    base[i] = 0;
-  }
-  if (tid == 0) *a.abort_word = 0;
-  for (int64_t i = tid; i < static_cast<int64_t>(W) * a.S; i += blockDim.x) {
+  const int64_t gid = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
+  const int64_t words = static_cast<int64_t>(W) * a.S;
+  for (int64_t i = gid; i < words; i += static_cast<int64_t>(gridDim.x) * kThreads) {
     a.pub[i] = 0;
     a.rel[i] = 0;
   }
-  // Rounds of R tokens: their k indices are staged in LDS by coalesced loads, then each thread
-  // numbers a contiguous run of the round's tokens per destination (entries in token order,
-  // k slots ascending), continuing from the destination's count of earlier rounds.
-  const int R = kPlanInts / a.k;
-  for (int r0 = 0; r0 < a.T; r0 += R) {
-    const int nr = min(R, a.T - r0);
-    __syncthreads();   // the previous round's reads of sidx and base are done
-    for (int i = tid; i < nr * a.k; i += blockDim.x) sidx[i] = a.idx[static_cast<int64_t>(r0) * a.k + i];
-    __syncthreads();
-    const int chunk = (nr + blockDim.x - 1) / blockDim.x;
-    const int t0 = min(nr, tid * chunk), t1 = min(nr, t0 + chunk);
-    for (int d = 0; d < W; ++d) {
-      const int lo = d * epw, hi = lo + epw;   // destination d's experts
-      int n = 0;
-      for (int t = t0; t < t1; ++t) {
-        int c = 0;
-        for (int j = 0; j < a.k; ++j) {
-          const int e = sidx[t * a.k + j];
-          c += e >= lo && e < hi;
-        }
-        n += a.dedup ? (c > 0) : c;
-      }
-      int round_total;
-      const int b = base[d];   // read before the scan's barriers; thread 0 advances it after them
-      int next = b + block_exclusive_scan(n, wsum, round_total);
-      for (int t = t0; t < t1; ++t) {
-        bool any = false;
-        for (int j = 0; j < a.k; ++j) {
-          const int e = sidx[t * a.k + j];
-          if (e >= lo && e < hi) {
-            a.entry_no[static_cast<int64_t>(r0 + t) * a.k + j] = a.dedup ? next : next++;
-            any = true;
-          }
-        }
-        if (a.dedup && any) ++next;
-      }
-      if (tid == 0) base[d] = b + round_total;
+  if (gid == 0) *a.abort_word = 0;
+  const int lane = threadIdx.x & 63;
+  const int c = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
+  if (c * kChunk >= a.T) return;
+  const int t = c * kChunk + lane;
+  const int* idx = a.idx + static_cast<int64_t>(t) * a.k;
+  int* no = a.entry_no + static_cast<int64_t>(t) * a.k;
+  // the token's destinations, held in registers (reading the indices again for every destination
+  // took 22 us at 2048 tokens, k = 8, W = 8)
+  int dst[kMaxK];
+#pragma unroll
+  for (int j = 0; j < kMaxK; ++j) dst[j] = j < a.k && t < a.T ? idx[j] : -1;
+#pragma unroll
+  for (int j = 0; j < kMaxK; ++j)
+    if (j < a.k) dst[j] = dst[j] >= 0 && dst[j] < a.E ? dst[j] / epw : -1;
+  const uint64_t below = (1ull << lane) - 1;
+  const int bits = a.dedup ? 1 : 32 - __builtin_clz(a.k);
+  for (int d = 0; d < W; ++d) {
+    int n = 0;
+#pragma unroll
+    for (int j = 0; j < kMaxK; ++j)
+      if (j < a.k) n += dst[j] == d;
+    if (a.dedup) n = n > 0;
+    int before = 0, all = 0;
+    for (int b = 0; b < bits; ++b) {
+      const uint64_t m = __ballot((n >> b) & 1);
+      before += __builtin_popcountll(m & below) << b;
+      all += __builtin_popcountll(m) << b;
     }
+#pragma unroll
+    for (int j = 0; j < kMaxK; ++j)
+      if (j < a.k && dst[j] == d) {
+        no[j] = before;
+        before += !a.dedup;
+      }
+    if (lane == 0) a.chunk_base[static_cast<int64_t>(c) * W + d] = all;
   }
-  __syncthreads();
-  for (int d = tid; d < W; d += blockDim.x) {
-    a.total[d * kLine] = base[d];
-    if (a.stats) {
-      a.stats[d] = base[d];
-      a.stats[W + d] = 0;
+}
+
+// The chunks' counts -> bases, and the totals: one wave per ring.
+__global__ __launch_bounds__(1024) void ring_scan_kernel(RingArgs a) {
+  const int W = a.win.n, lane = threadIdx.x & 63;
+  const int chunks = (a.T + kChunk - 1) / kChunk;
+  for (int d = threadIdx.x >> 6; d < W; d += 16) {
+    int base = 0;
+    for (int c0 = 0; c0 < chunks; c0 += 64) {
+      int* p = a.chunk_base + static_cast<int64_t>(c0 + lane) * W + d;
+      const int v = c0 + lane < chunks ? *p : 0;
+      int x = v;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(x, o);
+        if (lane >= o) x += y;
+      }
+      if (c0 + lane < chunks) *p = base + x - v;
+      base += __shfl(x, 63);
+    }
+    if (lane == 0) {
+      a.total[d * kLine] = base;
+      if (a.stats) {
+        a.stats[d] = base;
+        a.stats[W + d] = 0;
+      }
     }
   }
 }
@@ -174,171 +163,181 @@ __device__ __forceinline__ int bcast(int v) { return __builtin_amdgcn_readfirstl
 
 typedef __attribute__((address_space(1))) u32x4 gv4;
 
-// Consume entries [m0, m0 + nb) of ring d (claimed by this wave, nb <= min(64, S)): wait
-// until all are published, one acquire, one read of each ring row with one store per listed
-// window row, one release, then the nb slot releases. nb <= S, so no entry of the batch
-// waits on a slot the batch itself holds. False on abort. Wave-uniform control flow.
-__device__ bool consume(const RingArgs& a, int d, int m0, int nb, int lane) {
-  const int m = m0 + min(lane, nb - 1);
-  const int* pub_i = a.pub + static_cast<int64_t>(d) * a.S + m % a.S;
-  const int want = m / a.S + 1;
-  if (__ballot(lane < nb && __hip_atomic_load(pub_i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != want)) {
-    const uint64_t t0 = wall_ticks();
-    for (int it = 1;; ++it) {
-      const bool pending =
-          __ballot(lane < nb && __hip_atomic_load(pub_i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != want) != 0;
-      if (!pending) break;
+// A buffer over one ring slot (wave-uniform address).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t slot_buffer(const RingArgs& a, int d, int s) {
+  const uint64_t p = reinterpret_cast<uint64_t>(a.ring[d] + static_cast<int64_t>(s) * a.slot_bytes);
+  const uint64_t u = static_cast<uint64_t>(static_cast<uint32_t>(bcast(static_cast<int>(p)))) |
+                     static_cast<uint64_t>(static_cast<uint32_t>(bcast(static_cast<int>(p >> 32)))) << 32;
+  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(u), 0, static_cast<int>(a.slot_bytes), 0x00020000);
+}
+
+// Copies published entry m of ring d out and releases its slot (wave-uniform m, d).
+__device__ __forceinline__ void consume(const RingArgs& a, int d, int m, int lane) {
+  const int s = m % a.S;
+  const auto slot = slot_buffer(a, d, s);
+  const int pieces = a.row_bytes >> 4;
+  const int word = lane <= a.k ? __builtin_amdgcn_raw_buffer_load_b32(slot, a.row_bytes + 4 * lane, 0, kCoherent) : 0;
+  int n = 0, my_row = -1;
+  for (int p0 = 0; p0 < pieces; p0 += 64 * kPieces) {
+    u32x4 v[kPieces];
+#pragma unroll
+    for (int q = 0; q < kPieces; ++q) {
+      const int p = p0 + q * 64 + lane;
+      if (p < pieces) v[q] = __builtin_amdgcn_raw_buffer_load_b128(slot, p * 16, 0, kCoherent);
+    }
+    if (p0 == 0) {
+      n = bcast(word);
+      if (n < 0 || n > a.k) {               // never written by a producer: report, copy nothing
+        if (lane == 0) set_status(a.status, XS_EBADINPUT);
+        n = 0;
+      }
+      my_row = __shfl(word, min(lane + 1, 63));
+    }
+    for (int i = 0; i < n; ++i) {
+      const int r = __shfl(my_row, i);
+      if (r < 0 || r >= a.win.cap[d]) {
+        if (lane == 0 && p0 == 0) set_status(a.status, XS_ECAPACITY);
+        continue;
+      }
+      char* dst = a.win.base[d] + static_cast<int64_t>(r) * a.win.stride[d];
+#pragma unroll
+      for (int q = 0; q < kPieces; ++q) {
+        const int p = p0 + q * 64 + lane;
+        if (p < pieces) *(gv4*)(dst + p * 16) = v[q];
+      }
+    }
+  }
+  // the stores above waited for the slot's loads (a load no row needed may be overwritten)
+  asm volatile("" ::: "memory");
+  if (lane == 0)
+    __hip_atomic_store(a.rel + static_cast<int64_t>(d) * a.S + s, m / a.S + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// Lane i of a consumer follows the entries m, m + step, ... of ring d; every published one is
+// consumed, in any order. Until all are consumed, or the call is aborted.
+__device__ __forceinline__ void consume_all(const RingArgs& a, int d, int m, int step, int lane) {
+  const int tot = d >= 0 ? a.total[d * kLine] : 0;
+  uint64_t t0 = wall_ticks();
+  for (int it = 1;; ++it) {
+    const bool left = m < tot;
+    if (!__ballot(left)) return;
+    const bool ready = left && __hip_atomic_load(a.pub + static_cast<int64_t>(d) * a.S + m % a.S, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_SYSTEM) == m / a.S + 1;
+    asm volatile("" ::: "memory");
+    uint64_t todo = __ballot(ready);
+    if (!todo) {
       int stop = 0;
       if (lane == 0) {
         if ((it & 15) == 0 && aborted(a)) stop = 1;
         else if (wall_ticks() - t0 > static_cast<uint64_t>(a.timeout_ticks)) { give_up(a); stop = 1; }
       }
-      if (bcast(stop)) return false;
-      __builtin_amdgcn_s_sleep(1);
+      if (bcast(stop)) return;
+      __builtin_amdgcn_s_sleep(2);
+      continue;
     }
+    for (; todo; todo &= todo - 1) {
+      const int i = __builtin_ctzll(todo);
+      consume(a, bcast(__shfl(d, i)), bcast(__shfl(m, i)), lane);
+    }
+    if (ready) m += step;
+    t0 = wall_ticks();
   }
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "");
-  const int pieces = a.row_bytes >> 4;
-  for (int b = 0; b < nb; ++b) {
-    const int mb = m0 + b;
-    const char* slot = a.ring[d] + static_cast<int64_t>(mb % a.S) * a.slot_bytes;
-    const int* h = reinterpret_cast<const int*>(slot + a.row_bytes);
-    int n = bcast(lane == 0 ? h[0] : 0);
-    if (n < 0 || n > a.k) {               // never written by a producer: report, copy nothing
-      if (lane == 0) set_status(a.status, XS_EBADINPUT);
-      n = 0;
-    }
-    const int my_row = lane < n ? h[1 + lane] : -1;
-    for (int p0 = 0; p0 < pieces; p0 += 64 * 8) {
-      u32x4 v[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int p = p0 + q * 64 + lane;
-        if (p < pieces) v[q] = *(const gv4*)(slot + p * 16);
-      }
-      for (int i = 0; i < n; ++i) {
-        const int r = __shfl(my_row, i);
-        if (r < 0 || r >= a.win.cap[d]) {
-          if (lane == 0 && p0 == 0) set_status(a.status, XS_ECAPACITY);
-          continue;
-        }
-        char* dst = a.win.base[d] + static_cast<int64_t>(r) * a.win.stride[d];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          const int p = p0 + q * 64 + lane;
-          if (p < pieces) *(gv4*)(dst + p * 16) = v[q];
-        }
-      }
-    }
-  }
-  // every lane's reads of the slots are done before they are released
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
-  if (lane < nb)
-    __hip_atomic_store(a.rel + static_cast<int64_t>(d) * a.S + m % a.S, m / a.S + 1, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_SYSTEM);
-  return true;
 }
 
-// Entries a producer has written but not yet published: lane i < n holds the i-th flag and
-// its value. One release fence makes all of them visible; a producer publishes before it
-// ever waits, so no consumer waits on an entry whose producer is itself waiting.
-constexpr int kPend = 32;
-struct Pending {
-  int* flag;
-  int val;
-  int n;
-};
-
-__device__ __forceinline__ void publish(Pending& p, int lane) {
-  if (p.n == 0) return;
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
-  if (lane < p.n) __hip_atomic_store(p.flag, p.val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-  p.n = 0;
-}
-
-// Produce entry e of token t into ring d: the window rows of the lanes in `mask` (each lane j
-// holds slot j's row in my_row). The entry is left pending. False on abort.
-__device__ bool produce(const RingArgs& a, int t, int d, int e, uint64_t mask, int my_row, int lane, Pending& pend) {
-  const int s = e % a.S;
-  const int u = e / a.S;
-  int* rel = a.rel + static_cast<int64_t>(d) * a.S + s;
-  int* pub = a.pub + static_cast<int64_t>(d) * a.S + s;
-  bool stalled = false;
-  const uint64_t t0 = wall_ticks();
-  for (int it = 0;; ++it) {
-    // 1 slot free, 0 abort, 2 help with entry m, 3 wait
-    int st = 3, m = 0;
-    if (lane == 0) {
-      if (__hip_atomic_load(rel, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == u) {
-        st = 1;
-      } else if ((it & 15) == 15 && aborted(a)) {
-        st = 0;
-      } else if (wall_ticks() - t0 > static_cast<uint64_t>(a.timeout_ticks)) {
-        give_up(a);
-        st = 0;
-      } else {
-        m = __hip_atomic_load(a.tail + d * kLine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (m <= e - a.S && m < a.total[d * kLine] &&
-            __hip_atomic_compare_exchange_strong(a.tail + d * kLine, &m, m + 1, __ATOMIC_RELAXED,
-                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-          st = 2;
-        else
-          __builtin_amdgcn_s_sleep(1);
-      }
-    }
-    st = bcast(st);
-    m = bcast(m);
-    if (st == 1) break;
-    if (st == 0) return false;
-    if (!stalled) publish(pend, lane);     // never wait holding unpublished entries
-    stalled = true;
-    if (st == 2 && !consume(a, d, m, 1, lane)) return false;
+// Produces token t's entries: lane j holds slot j's destination (d, -1: none), window row and entry
+// number. Every entry whose slot is free is written, then all of them are published; until none
+// is left. False on abort.
+__device__ __forceinline__ bool produce(const RingArgs& a, int t, int d, int en, int row, int lane) {
+  // the first lane of each entry stands for it, with the entry's lanes in `mask`
+  uint64_t mask = 0, todo = 0;
+  for (uint64_t rest = __ballot(d >= 0); rest;) {
+    const int lead = __builtin_ctzll(rest);
+    const int dd = __shfl(d, lead);
+    const uint64_t m = a.dedup ? __ballot(d == dd) : 1ull << lead;
+    if ((m >> lane) & 1) mask = m;
+    todo |= 1ull << lead;
+    rest &= ~m;
   }
-  // only orders this wave's stores below after the observation (a write after the last
-  // reader's reads): nothing is read here, so no cache maintenance
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-  if (stalled && lane == 0 && a.stats) atomicAdd(a.stats + a.win.n + d, 1);
-  char* slot = a.ring[d] + static_cast<int64_t>(s) * a.slot_bytes;
+  const int s = d >= 0 ? en % a.S : 0, u = d >= 0 ? en / a.S : 0;
+  const int64_t word = d >= 0 ? static_cast<int64_t>(d) * a.S + s : 0;
   const char* src = a.x + static_cast<int64_t>(t) * a.x_stride;
   const int pieces = a.row_bytes >> 4;
-  for (int p0 = 0; p0 < pieces; p0 += 64 * 8) {
-    u32x4 v[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int p = p0 + q * 64 + lane;
-      if (p < pieces) v[q] = *(const gv4*)(src + p * 16);
+  uint64_t t0 = wall_ticks();
+  for (int it = 0; todo; ++it) {
+    const bool wait = (todo >> lane) & 1;
+    // a slot's first use needs no look
+    const bool ready = wait && (u == 0 || __hip_atomic_load(a.rel + word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == u);
+    asm volatile("" ::: "memory");
+    if (it == 0 && wait && !ready && a.stats) atomicAdd(a.stats + a.win.n + d, 1);
+    const uint64_t now = __ballot(ready);
+    if (!now) {
+      int stop = 0;
+      if (lane == 0) {
+        if ((it & 15) == 15 && aborted(a)) stop = 1;
+        else if (wall_ticks() - t0 > static_cast<uint64_t>(a.timeout_ticks)) { give_up(a); stop = 1; }
+      }
+      if (bcast(stop)) return false;
+      __builtin_amdgcn_s_sleep(4);
+      continue;
     }
+    for (int p0 = 0; p0 < pieces; p0 += 64 * kPieces) {
+      u32x4 v[kPieces];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int p = p0 + q * 64 + lane;
-      if (p < pieces) *(gv4*)(slot + p * 16) = v[q];
+      for (int q = 0; q < kPieces; ++q) {
+        const int p = p0 + q * 64 + lane;
+        if (p < pieces) v[q] = *(const gv4*)(src + p * 16);
+      }
+      for (uint64_t w = now; w; w &= w - 1) {
+        const int i = __builtin_ctzll(w);
+        const auto slot = slot_buffer(a, bcast(__shfl(d, i)), bcast(__shfl(s, i)));
+#pragma unroll
+        for (int q = 0; q < kPieces; ++q) {
+          const int p = p0 + q * 64 + lane;
+          if (p < pieces) __builtin_amdgcn_raw_buffer_store_b128(v[q], slot, p * 16, 0, kCoherent);
+        }
+      }
     }
+    // headers: the number of rows, then the rows in ascending k slot order
+    for (uint64_t w = now; w; w &= w - 1) {
+      const int i = __builtin_ctzll(w);
+      const auto slot = slot_buffer(a, bcast(__shfl(d, i)), bcast(__shfl(s, i)));
+      const uint64_t m = static_cast<uint64_t>(static_cast<uint32_t>(__shfl(static_cast<int>(mask), i))) |
+                         static_cast<uint64_t>(static_cast<uint32_t>(__shfl(static_cast<int>(mask >> 32), i))) << 32;
+      if ((m >> lane) & 1)
+        __builtin_amdgcn_raw_buffer_store_b32(row, slot, a.row_bytes + 4 * (1 + __builtin_popcountll(m & ((1ull << lane) - 1))),
+                                              0, kCoherent);
+      if (lane == 0) __builtin_amdgcn_raw_buffer_store_b32(__builtin_popcountll(m), slot, a.row_bytes, 0, kCoherent);
+    }
+    // published once every store of this wave has reached memory
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (ready) __hip_atomic_store(a.pub + word, u + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    todo &= ~now;
+    t0 = wall_ticks();
   }
-  // header: the number of rows, then the rows in ascending k slot order
-  int* hdr = reinterpret_cast<int*>(slot + a.row_bytes);
-  if ((mask >> lane) & 1ull) hdr[1 + __builtin_popcountll(mask & ((1ull << lane) - 1))] = my_row;
-  if (lane == 0) hdr[0] = __builtin_popcountll(mask);
-  if (lane == pend.n) {
-    pend.flag = pub;
-    pend.val = u + 1;
-  }
-  if (++pend.n == kPend) publish(pend, lane);
   return true;
 }
 
-__global__ __launch_bounds__(kThreads) void ring_dispatch_kernel(RingArgs a) {
+// four waves per SIMD, two of them this call's: a second call on another stream is resident too
+__global__ __launch_bounds__(kThreads, 4) void ring_dispatch_kernel(RingArgs a) {
   const int lane = threadIdx.x & 63;
   const int agents = gridDim.x * (kThreads / 64);
-  const int me = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
+  const int me = bcast(blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6));
   const int W = a.win.n;
   const int epw = a.E / W;
-  // Odd waves consume from the start (the receivers), even waves produce in token order: a
-  // full ring then drains at the consumers' rate rather than through stalled producers'
-  // help. Both drain at the end.
-  const bool consumer = agents > 1 && (me & 1);
-  const int producers = agents > 1 ? agents / 2 : 1;
-  Pending pend{nullptr, 0, 0};
-  for (int t = consumer ? a.T : (agents > 1 ? me / 2 : me); t < a.T; t += producers) {
+  const int half = agents / 2, id = me / 2;
+  if (me & 1) {
+    if (half >= W) {
+      // ring id % W; of its consumers as many as it has slots (no more entries are ever ready)
+      const int d = id % W, q = id / W;
+      const int Q = min((half - d + W - 1) / W, a.S);
+      if (q < Q) consume_all(a, lane < kLook ? d : -1, q + lane * Q, kLook * Q, lane);
+    } else {
+      const int d = id + lane * half;
+      consume_all(a, lane < XS_MAX_WINDOWS && d < W ? d : -1, 0, 1, lane);
+    }
+    return;
+  }
+  for (int t = id; t < a.T; t += half) {
     // lane j < k holds slot j's destination, window row and entry number
     int d = -1, r = -1, en = 0;
     if (lane < a.k) {
@@ -349,38 +348,10 @@ __global__ __launch_bounds__(kThreads) void ring_dispatch_kernel(RingArgs a) {
       } else {
         d = e / epw;
         r = a.slot_row[q];
-        en = a.entry_no[q];
+        en = a.entry_no[q] + a.chunk_base[static_cast<int64_t>(t / kChunk) * W + d];
       }
     }
-    uint64_t todo = __ballot(d >= 0);
-    while (todo) {
-      const int lead = __builtin_ctzll(todo);
-      const int dd = __shfl(d, lead);
-      // the entry's lanes: this slot alone, or every slot of the token on destination dd
-      const uint64_t mask = a.dedup ? __ballot(d == dd) : (1ull << lead);
-      todo &= ~mask;
-      if (!produce(a, t, dd, __shfl(en, lead), mask, r, lane, pend)) return;
-    }
-  }
-  publish(pend, lane);
-  // drain: consume whatever is left, ring by ring, claiming up to kBatch (kBatchWide in wide
-  // rings) entries per atomic (never more than S: see consume)
-  const int batch = min(a.S >= kWideRing ? kBatchWide : kBatch, a.S);
-  for (int i = 0; i < W; ++i) {
-    const int d = (me + i) % W;
-    const int tot = a.total[d * kLine];
-    for (;;) {
-      int m = 0, ok = 1;
-      if (lane == 0) {
-        ok = aborted(a) ? 0 : 1;
-        m = __hip_atomic_load(a.tail + d * kLine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        m = m < tot ? atomicAdd(a.tail + d * kLine, batch) : tot;
-      }
-      if (!bcast(ok)) return;
-      m = bcast(m);
-      if (m >= tot) break;
-      if (!consume(a, d, m, min(batch, tot - m), lane)) return;
-    }
+    if (!produce(a, t, d, en, r, lane)) return;
   }
 }
 
@@ -397,13 +368,13 @@ namespace {
 
 int64_t align16(int64_t v) { return (v + 15) / 16 * 16; }
 
-// Control block in the workspace: tail and total [W] each, one counter per 128-byte line, the
-// abort word on a line of its own, then pub and rel [W][S] each.
-constexpr int64_t kCtrlTail = 0, kCtrlTotal = XS_MAX_WINDOWS * 32, kCtrlAbort = 2 * XS_MAX_WINDOWS * 32,
-                  kCtrlPub = 2 * XS_MAX_WINDOWS * 32 + 32;
-// control words, then the entry numbers [T][k]
+// Control block in the workspace: total [W], one counter per 128-byte line, the abort word on a
+// line of its own, then pub and rel [W][S] each.
+constexpr int64_t kCtrlTotal = 0, kCtrlAbort = XS_MAX_WINDOWS * 32, kCtrlPub = kCtrlAbort + 32;
+int64_t chunks_of(int32_t T) { return (static_cast<int64_t>(T) + xs::ring::kChunk - 1) / xs::ring::kChunk; }
+// control words, then the entry numbers [T][k] and the chunk bases [chunks][W]
 int64_t ctrl_ints(int32_t T, int32_t k, int32_t W, int32_t S) {
-  return kCtrlPub + 2 * static_cast<int64_t>(W) * S + static_cast<int64_t>(T) * k;
+  return kCtrlPub + 2 * static_cast<int64_t>(W) * S + static_cast<int64_t>(T) * k + chunks_of(T) * W;
 }
 
 }  // namespace
@@ -462,21 +433,27 @@ extern "C" int xs_dispatch_ring(const void* x, int32_t T, int32_t H, const int32
   a.idx = topk_idx;
   a.slot_row = slot_row;
   a.slot_bytes = rings[0].row_stride_bytes;
-  a.tail = ctrl + kCtrlTail;
   a.total = ctrl + kCtrlTotal;
   a.abort_word = ctrl + kCtrlAbort;
   a.pub = ctrl + kCtrlPub;
   a.rel = a.pub + static_cast<int64_t>(W) * S;
   a.entry_no = a.rel + static_cast<int64_t>(W) * S;
+  a.chunk_base = a.entry_no + static_cast<int64_t>(T) * k;
   a.stats = stats;
   a.status = dev_status;
   a.timeout_ticks = xs_host::ns_to_ticks((spin_timeout_us > 0 ? spin_timeout_us : 2000000) * 1000);
   hipStream_t st = static_cast<hipStream_t>(stream);
-  hipLaunchKernelGGL(ring::ring_plan_kernel, dim3(1), dim3(1024), 0, st, a);
+  if (T > 0) {
+    // a wave per chunk of tokens, and enough threads to clear the slots' words
+    const int64_t blocks = std::max((chunks_of(T) + 3) / 4, std::min<int64_t>(1024, static_cast<int64_t>(W) * S / 1024));
+    hipLaunchKernelGGL(ring::ring_rank_kernel, dim3(static_cast<unsigned>(blocks)), dim3(ring::kThreads), 0, st, a);
+    if (xs_host::launch_status()) return XS_EHIP;
+  }
+  hipLaunchKernelGGL(ring::ring_scan_kernel, dim3(1), dim3(1024), 0, st, a);
   if (xs_host::launch_status()) return XS_EHIP;
   if (T > 0) {
-    // two workgroups (eight agent waves) per CU, all resident
-    const int grid = std::min((T + 3) / 4, 2 * xs_host::persistent_grid(max_producers));
+    // two workgroups (eight agent waves) per CU, all resident; no more than a producer per token
+    const int grid = std::min((T + 1) / 2, 2 * xs_host::persistent_grid(max_producers));
     hipLaunchKernelGGL(ring::ring_dispatch_kernel, dim3(grid), dim3(ring::kThreads), 0, st, a);
     if (xs_host::launch_status()) return XS_EHIP;
   }

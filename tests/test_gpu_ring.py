@@ -94,6 +94,20 @@ def test_ring_windows_equal_plain_dispatch(S, dedup):
     assert all(0 <= s <= n for s, n in zip(stats[W:], stats[:W]))
 
 
+# fewer consumer waves than rings (few tokens), more consumers than slots, the edges of the 64-token
+# numbering chunks, a row longer than one pass of a wave (512 16-byte pieces), k = 32
+@pytest.mark.parametrize("T,H,E,k,W,S", [(1, 64, 64, 32, 64, 1), (3, 8, 64, 5, 32, 2), (64, 64, 16, 4, 16, 3),
+                                         (65, 4104, 8, 8, 2, 4), (129, 24, 128, 32, 64, 1), (1000, 64, 64, 6, 1, 7)])
+@pytest.mark.parametrize("dedup", [0, 1])
+def test_ring_agent_layouts(T, H, E, k, W, S, dedup):
+    idx, sr, cap, x = _setup(T, H, E, k, W, T + k)
+    got, st, stats = _ring_dispatch(x, idx, sr, E, W, cap, S, dedup)
+    assert st == 0
+    want, _ = oep.dispatch(x[None], idx[None], sr[None], E, W, cap)
+    assert np.array_equal(got, want)
+    assert stats[:W].tolist() == [len(e) for e in oring.ring_entries(idx, sr, E, W, bool(dedup))]
+
+
 @pytest.mark.parametrize("dedup", [0, 1])
 def test_ring_host_coherent_memory(dedup):
     T, H, E, k, W = 200, 512, 16, 3, 4

@@ -52,6 +52,35 @@ __device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 
 
 __device__ __forceinline__ uint64_t wall_ticks() { return wall_clock64(); }
 
+// ------------------------------------------------------------------- direct loads into LDS
+typedef __attribute__((address_space(3))) char lds_char;
+typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
+typedef int v4i __attribute__((ext_vector_type(4)));
+
+// A raw buffer descriptor over [base, base + bytes): loads past its end fetch nothing.
+__device__ __forceinline__ v4i buffer_rsrc(const void* base, uint32_t bytes) {
+  const uint64_t b = reinterpret_cast<uint64_t>(base);
+  const v4i r = {static_cast<int>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b))),
+                 static_cast<int>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b >> 32)) & 0xFFFF),
+                 static_cast<int>(__builtin_amdgcn_readfirstlane(bytes)), 0x00020000};
+  return r;
+}
+
+// One 16-byte piece per lane from the buffer at voff into LDS at dst + 16 lane. Issued from
+// assembly so that the compiler does not count it (it would wait for every load in flight
+// before each LDS read); the kernel waits itself, with vmcnt.
+__device__ __forceinline__ void load_lds16(v4i rsrc, uint32_t voff, const lds_char* dst) {
+  const uint32_t m0v = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(dst));
+  asm volatile("buffer_load_dwordx4 %0, %1, 0 offen lds" :: "v"(voff), "s"(rsrc), "{m0}"(m0v) : "memory");
+}
+
+template <int V>
+__device__ __forceinline__ void wait_vm() {   // s_waitcnt vmcnt(V) only
+  static_assert(V >= 0 && V < 64);
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (V & 15) | ((V >> 4) << 14));
+  asm volatile("" ::: "memory");
+}
+
 // Busy-wait for `ticks` wall-clock ticks without touching memory.
 __device__ __forceinline__ void spin_ticks(uint64_t ticks) {
   if (!ticks) return;

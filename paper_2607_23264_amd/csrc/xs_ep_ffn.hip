@@ -26,7 +26,7 @@
 #include <cmath>
 #include <mutex>
 
-#include "xs_gemm_mx.hpp"
+#include "xs_gemm_small.hpp"
 #include "xs_plan.hpp"
 
 namespace xs {
@@ -63,6 +63,7 @@ struct EpArgs {
   int* l1_done;
   int* claim_ctr;              // [0] Linear-1 / wave-list entries taken, [1] Linear-2 entries taken
   int claim;                   // XS_CLAIM_STATIC / XS_CLAIM_DYNAMIC
+  int small1, small2;          // Linear-1 / Linear-2 tiles of at most kSmallRows rows take the small-tile core
   int l2_combine;              // Linear-2 epilogue: 1 = combine windows, 0 = y rows
   int policy, lead, chunk, withhold_row;
   int64_t gap_ticks, timeout_ticks;
@@ -216,14 +217,26 @@ __device__ __forceinline__ void ep_l1_tile(const EpArgs& a, int p, int nt, bool 
   const uint16_t* A = reinterpret_cast<const uint16_t*>(
       a.dwin.base[dl] + static_cast<int64_t>(a.expert_offsets[e] + m0) * a.dwin.stride[dl]);
   const uint16_t* B = a.w1 + static_cast<int64_t>(x) * 2 * a.I * a.H;
-  Acc acc;
-  gemm_mainloop<true>(A, lda, rows, B, a.H, nt * (kBN / 2), a.I, true, a.H, acc, lds);
-  claim_load(a, cl);
-  const uint64_t t1 = a.tr.buf ? wall_ticks() : 0;
-  if (tid < rows)
-    rowptr[tid] = reinterpret_cast<char*>(
-        a.h + static_cast<int64_t>(a.exp_hrow[x] + m0 + tid) * a.I + nt * (kBN / 2));
-  stage_swiglu(acc, lds);
+  const auto put_rows = [&] {
+    claim_load(a, cl);
+    const uint64_t t = a.tr.buf ? wall_ticks() : 0;
+    if (tid < rows)
+      rowptr[tid] = reinterpret_cast<char*>(
+          a.h + static_cast<int64_t>(a.exp_hrow[x] + m0 + tid) * a.I + nt * (kBN / 2));
+    return t;
+  };
+  uint64_t t1;
+  if (a.small1 && rows <= kSmallRows) {
+    AccSmall acc;
+    const int ni = gemm_mainloop_small(A, lda, rows, B, a.H, nt * (kBN / 2), a.I, true, a.H, acc, lds);
+    t1 = put_rows();
+    stage_swiglu_small(acc, ni, lds);
+  } else {
+    Acc acc;
+    gemm_mainloop<true>(A, lda, rows, B, a.H, nt * (kBN / 2), a.I, true, a.H, acc, lds);
+    t1 = put_rows();
+    stage_swiglu(acc, lds);
+  }
   __syncthreads();
   claim_take(a, cl);
   store_rows(lds, kEpiPitchH, kBN / 2, rows, rowptr);
@@ -287,11 +300,10 @@ __device__ __forceinline__ void ep_l2_tile(const EpArgs& a, int p, int nt, bool 
   int code = -1;
   if (a.l2_combine && tid < rows)
     code = a.row_src[static_cast<int64_t>(e / a.epw) * a.cap + a.expert_offsets[e] + m0 + tid];
-  Acc acc;
-  gemm_mainloop<true>(A, a.I, rows, B, a.I, n0, 0, false, a.I, acc, lds);
-  claim_load(a, cl);
-  const uint64_t t1 = a.tr.buf ? wall_ticks() : 0;
-  if (tid < rows) {
+  const auto put_rows = [&] {
+    claim_load(a, cl);
+    const uint64_t t = a.tr.buf ? wall_ticks() : 0;
+    if (tid >= rows) return t;
     char* ptr;
     if (a.l2_combine) {
       const int src = code >> 24, slot = code & 0xffffff;
@@ -306,8 +318,20 @@ __device__ __forceinline__ void ep_l2_tile(const EpArgs& a, int p, int nt, bool 
       ptr = reinterpret_cast<char*>(a.y + static_cast<int64_t>(a.exp_hrow[x] + m0 + tid) * a.H + n0);
     }
     rowptr[tid] = ptr;
+    return t;
+  };
+  uint64_t t1;
+  if (a.small2 && rows <= kSmallRows) {
+    AccSmall acc;
+    const int ni = gemm_mainloop_small(A, a.I, rows, B, a.I, n0, 0, false, a.I, acc, lds);
+    t1 = put_rows();
+    stage_tile_small(acc, ni, lds);
+  } else {
+    Acc acc;
+    gemm_mainloop<true>(A, a.I, rows, B, a.I, n0, 0, false, a.I, acc, lds);
+    t1 = put_rows();
+    stage_tile(acc, lds);
   }
-  stage_tile(acc, lds);
   __syncthreads();
   claim_take(a, cl);
   store_rows(lds, kEpiPitch, kBN, rows, rowptr);
@@ -350,15 +374,29 @@ __device__ __forceinline__ void ep_l1_tile_mx(const EpArgs& a, int p, int nt, bo
   const int64_t ldb = BF4 ? a.H / 2 : a.H;
   const uint8_t* B = reinterpret_cast<const uint8_t*>(a.w1) + wrows * ldb;
   const uint8_t* Bs = a.w1s + wrows * 16;
-  AccMx acc;
-  gemm_mainloop_mx<BF4>(A, ws, A + a.H, ws, 16, rows, B, ldb, Bs, 16, static_cast<int64_t>(a.n_experts) * 2 * a.I * 16,
-                        nt * (kBN / 2), a.I, true, a.H, acc, lds);
-  claim_load(a, cl);
-  const uint64_t t1 = a.tr.buf ? wall_ticks() : 0;
-  const int tid = tid_here();   // not held across the mainloop
+  const int64_t bs_grp = static_cast<int64_t>(a.n_experts) * 2 * a.I * 16;
   const int64_t hrow0 = static_cast<int64_t>(a.exp_hrow[x] + m0);
-  if (tid < rows) rowptr[tid] = reinterpret_cast<char*>(a.h) + (hrow0 + tid) * a.h_stride;
-  stage_swiglu_mxq(acc, lds);
+  const auto put_rows = [&] {
+    claim_load(a, cl);
+    const uint64_t t = a.tr.buf ? wall_ticks() : 0;
+    const int tid = tid_here();   // not held across the mainloop
+    if (tid < rows) rowptr[tid] = reinterpret_cast<char*>(a.h) + (hrow0 + tid) * a.h_stride;
+    return t;
+  };
+  uint64_t t1;
+  if (a.small1 && rows <= kSmallRows) {
+    AccMxSmall acc;
+    const int ni = gemm_mainloop_mx_small<BF4>(A, ws, A + a.H, ws, 16, rows, B, ldb, Bs, 16, bs_grp, nt * (kBN / 2), a.I,
+                                               true, a.H, acc, lds);
+    t1 = put_rows();
+    stage_swiglu_mxq_small(acc, ni, lds);
+  } else {
+    AccMx acc;
+    gemm_mainloop_mx<BF4>(A, ws, A + a.H, ws, 16, rows, B, ldb, Bs, 16, bs_grp, nt * (kBN / 2), a.I, true, a.H, acc, lds);
+    t1 = put_rows();
+    stage_swiglu_mxq(acc, lds);
+  }
+  const int tid = tid_here();
   __syncthreads();
   claim_take(a, cl);
   typedef __attribute__((address_space(1))) u32x4 global_u32x4;
@@ -420,13 +458,12 @@ __device__ __forceinline__ void ep_l2_tile_mx(const EpArgs& a, int p, int nt, bo
   int code = -1;
   if (a.l2_combine && static_cast<int>(threadIdx.x) < rows)
     code = a.row_src[static_cast<int64_t>(e / a.epw) * a.cap + a.expert_offsets[e] + m0 + threadIdx.x];
-  AccMx acc;
-  gemm_mainloop_mx<BF4>(A, a.h_stride, As, 16, a.h_rows * 16, rows, B, ldb, Bs, 16,
-                        static_cast<int64_t>(a.n_experts) * a.H * 16, n0, 0, false, a.I, acc, lds);
-  claim_load(a, cl);
-  const uint64_t t1 = a.tr.buf ? wall_ticks() : 0;
-  const int tid = tid_here();   // not held across the mainloop
-  if (tid < rows) {
+  const int64_t bs_grp = static_cast<int64_t>(a.n_experts) * a.H * 16;
+  const auto put_rows = [&] {
+    claim_load(a, cl);
+    const uint64_t t = a.tr.buf ? wall_ticks() : 0;
+    const int tid = tid_here();   // not held across the mainloop
+    if (tid >= rows) return t;
     char* ptr = nullptr;
     const int src = code >> 24, slot = code & 0xffffff;
     if (code >= 0 && src < a.n_src && slot < a.tk)
@@ -434,8 +471,22 @@ __device__ __forceinline__ void ep_l2_tile_mx(const EpArgs& a, int p, int nt, bo
     else
       set_status(a.status, XS_EBADINPUT);
     rowptr[tid] = ptr;
+    return t;
+  };
+  uint64_t t1;
+  if (a.small2 && rows <= kSmallRows) {
+    AccMxSmall acc;
+    const int ni = gemm_mainloop_mx_small<BF4>(A, a.h_stride, As, 16, a.h_rows * 16, rows, B, ldb, Bs, 16, bs_grp, n0, 0,
+                                               false, a.I, acc, lds);
+    t1 = put_rows();
+    stage_tile_mx_small(acc, ni, lds);
+  } else {
+    AccMx acc;
+    gemm_mainloop_mx<BF4>(A, a.h_stride, As, 16, a.h_rows * 16, rows, B, ldb, Bs, 16, bs_grp, n0, 0, false, a.I, acc, lds);
+    t1 = put_rows();
+    stage_tile_mx(acc, lds);
   }
-  stage_tile_mx(acc, lds);
+  const int tid = tid_here();
   __syncthreads();
   claim_take(a, cl);
   store_rows_n<kMxThreads>(lds, kEpiPitch * 2, kBN * 2 / 16, rows, rowptr);
@@ -891,6 +942,17 @@ int fill_args(const xs_ep_layer* L, void* workspace, EpArgs* a, WinSet* dws, Win
   a->h_stride = h_row_bytes(L);
   a->h_rows = L->h_rows;
   a->hs = is_mx(L) ? static_cast<uint8_t*>(L->h_ws) + L->h_rows * static_cast<int64_t>(L->I) : nullptr;
+  // the small-tile core addresses an expert's weights, a tile's activation rows and their scale
+  // groups by 31-bit offsets
+  const auto fits = [](int64_t n) { return n < (int64_t{1} << 31); };
+  int64_t row_stride = 0;
+  for (int d = 0; d < n_cwin_of(L); ++d) row_stride = std::max(row_stride, a->dwin.stride[d]);
+  const int64_t wb = is_mx(L) ? 1 : 2;
+  const bool weights = fits(2ll * L->I * L->H * wb);
+  a->small1 = weights && fits(kSmallRows * row_stride) &&
+              (!is_mx(L) || fits(static_cast<int64_t>(L->H) / 512 * L->n_experts * 2 * L->I * 16));
+  a->small2 = weights && (!is_mx(L) || (fits(static_cast<int64_t>(L->I) / 512 * L->n_experts * L->H * 16) &&
+                                        fits(static_cast<int64_t>(L->I) / 512 * L->h_rows * 16)));
   int* meta = reinterpret_cast<int*>(ws + w.meta_off);
   int* exp = reinterpret_cast<int*>(ws + w.exp_off);
   a->meta = meta;

@@ -419,40 +419,41 @@ constexpr int kHqScaleOff = kBM * kHqPitch;
 // columns (block 2 wn + jj of the tile); a lane holds 16 of a row's 32 values of that block
 // and lane ^ 32 the other 16, so the block maximum takes one half swap. Codes: the exact
 // power-of-two scaling and the hardware round-to-nearest-even E4M3 conversion.
+__device__ __forceinline__ void swiglu_mxq_block(const f32x16& gate, const f32x16& upv, int row, int block, int up,
+                                                 char* lds) {
+  typedef uint32_t u32x2_ __attribute__((ext_vector_type(2)));
+  float hv[16];
+  uint32_t amax = 0;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const float gt = gate[q], u = upv[q];
+    hv[q] = gt * __builtin_amdgcn_rcpf(1.f + __expf(-gt)) * u;
+    amax = max(amax, __builtin_bit_cast(uint32_t, hv[q]) & 0x7FFFFFFFu);
+  }
+  const auto r = __builtin_amdgcn_permlane32_swap(amax, amax, false, false);
+  const u32x2_ both = {r[0], r[1]};
+  const int e = mx_exp_e4m3_f32(max(both.x, both.y));
+  const int col0 = 32 * block + 4 * up;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    uint32_t c = static_cast<uint32_t>(__builtin_amdgcn_cvt_pk_fp8_f32(
+        __builtin_amdgcn_ldexpf(hv[4 * g], -e), __builtin_amdgcn_ldexpf(hv[4 * g + 1], -e), 0, false));
+    c = static_cast<uint32_t>(__builtin_amdgcn_cvt_pk_fp8_f32(
+        __builtin_amdgcn_ldexpf(hv[4 * g + 2], -e), __builtin_amdgcn_ldexpf(hv[4 * g + 3], -e),
+        static_cast<int>(c), true));
+    *reinterpret_cast<uint32_t*>(lds + row * kHqPitch + col0 + 8 * g) = c;
+  }
+  if (up == 0) lds[kHqScaleOff + row * 4 + block] = static_cast<char>(e + 127);
+}
+
 __device__ __forceinline__ void stage_swiglu_mxq(const AccMx& acc, char* lds) {
   const int lane = lane_id_here(), w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = w >> 1, wn = w & 1;
-  const int up = lane >> 5;
-  typedef uint32_t u32x2_ __attribute__((ext_vector_type(2)));
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = wm * 128 + 32 * i + (lane & 31);
+  for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int jj = 0; jj < 2; ++jj) {
-      float hv[16];
-      uint32_t amax = 0;
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const float gt = acc[i][2 * jj][q], u = acc[i][2 * jj + 1][q];
-        hv[q] = gt * __builtin_amdgcn_rcpf(1.f + __expf(-gt)) * u;
-        amax = max(amax, __builtin_bit_cast(uint32_t, hv[q]) & 0x7FFFFFFFu);
-      }
-      const auto r = __builtin_amdgcn_permlane32_swap(amax, amax, false, false);
-      const u32x2_ both = {r[0], r[1]};
-      const int e = mx_exp_e4m3_f32(max(both.x, both.y));
-      const int col0 = 32 * (2 * wn + jj) + 4 * up;
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        uint32_t c = static_cast<uint32_t>(__builtin_amdgcn_cvt_pk_fp8_f32(
-            __builtin_amdgcn_ldexpf(hv[4 * g], -e), __builtin_amdgcn_ldexpf(hv[4 * g + 1], -e), 0, false));
-        c = static_cast<uint32_t>(__builtin_amdgcn_cvt_pk_fp8_f32(
-            __builtin_amdgcn_ldexpf(hv[4 * g + 2], -e), __builtin_amdgcn_ldexpf(hv[4 * g + 3], -e),
-            static_cast<int>(c), true));
-        *reinterpret_cast<uint32_t*>(lds + row * kHqPitch + col0 + 8 * g) = c;
-      }
-      if (up == 0) lds[kHqScaleOff + row * 4 + 2 * wn + jj] = static_cast<char>(e + 127);
-    }
-  }
+    for (int jj = 0; jj < 2; ++jj)
+      swiglu_mxq_block(acc[i][2 * jj], acc[i][2 * jj + 1], wm * 128 + 32 * i + (lane & 31), 2 * wn + jj, lane >> 5, lds);
 }
 
 // Stores staged rows [0, rows) through per-row destination pointers (null rows skipped):

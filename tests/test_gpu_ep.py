@@ -309,6 +309,36 @@ def test_multi_source_ragged_share():
                     assert np.all(row == 0xFFFF)
 
 
+# experts with every kind of row block: one row, the edges of the 32-row MFMA blocks, of the 64- and
+# 128-row stages of the small-tile cores, and blocks above them
+@pytest.mark.parametrize("prec", ["BF16", "MXFP8", "W4A8"])
+def test_expert_rows_at_block_edges(prec):
+    from oracle import ep_mx as omx
+    from oracle import mx as omxf
+    from paper_2607_23264_amd.layer import EPLayer, Shape, pacing
+    X = xs()
+    loads = [1, 31, 32, 33, 64, 65, 96, 97, 128, 129, 255, 257]
+    cfg = synth.EPConfig("edges", T=sum(loads), H=512, E=len(loads), k=1, I=512, W=4, n_src=1, compute_all=True)
+    inp = synth.ep_inputs(cfg, 3)
+    expert = np.random.default_rng(5).permutation(np.repeat(np.arange(cfg.E), loads))
+    logits = np.zeros((1, cfg.T, cfg.E), np.float32)
+    logits[0, np.arange(cfg.T), expert] = 4.0
+    lay = EPLayer(Shape(1, cfg.T, cfg.H, cfg.E, 1, cfg.I, cfg.W, 0, cfg.E), precision=getattr(X, f"XS_PREC_{prec}"))
+    lay.upload(logits, inp["x"], inp["w1"], inp["w2"])
+    args = (inp["x"], logits, inp["w1"], inp["w2"], 1, cfg.E, cfg.W)
+    if prec == "BF16":
+        ref = oep.ep_layer(*args, cap=cfg.T)
+    else:
+        ref = omx.ep_layer_mx(*args, cap=cfg.T, wfmt=omxf.E2M1 if prec == "W4A8" else omxf.E4M3)
+    for p in (None, pacing(X.XS_POLICY_INTERLEAVE, lead=1, claim=X.XS_CLAIM_DYNAMIC, max_producers=9)):
+        lay.cwin.fill_(-1)
+        lay.fused(p)
+        torch.cuda.synchronize()
+        assert int(lay.status.item()) == 0
+        assert_close(host_bits(lay.cwin)[0], bits_f64(ref["combine"][0]), f"combine rows {prec}")
+        assert_close(host_bits(lay.out), ref["out64"], f"output {prec}")
+
+
 def _records(buf, count):
     n = min(int(count.item()), buf.shape[0])
     r = buf[:n].cpu().numpy().astype(np.uint64)

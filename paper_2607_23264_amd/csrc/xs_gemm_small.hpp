@@ -4,8 +4,9 @@
 // stages hold 64 or 128 rows, the LDS that is saved holds more stages (the loads in flight per
 // CU are what the weight stream's rate hangs on), and every wave multiplies all the rows by its
 // own share of the columns. One barrier per K step; the loads of stage kt + S - 1 go into the
-// slot of stage kt - 1, S stages in all. Loads past K are issued out of the buffers' range
-// (nothing is fetched), so the number in flight is the same in every step.
+// slot of stage kt - 1, S stages in all. Loads past K, and of activation rows that do not exist,
+// are issued out of the buffers' range: nothing is fetched (every line counts: a CU's load path
+// is what bounds the quantized tiles), and the number in flight is the same in every step.
 //
 // The products are summed by the same MFMAs in the same K order as in the 256-row cores: the
 // results' bits do not depend on which core ran.
@@ -17,6 +18,12 @@ namespace xs {
 constexpr int kSmallRows = 128;
 constexpr uint32_t kBufBytes = 0x80000000u;   // descriptors span 2 GiB; offsets from here on fetch nothing
 static_assert(kLdsBytes >= 4 * (64 + kBN) * kBK * 2, "four stages of 64 activation rows");
+
+// Per-lane offset o (kBufBytes for a row that does not exist) plus the K offset k, or, past the
+// last stage, out of range. (The or keeps a missing row's offset from wrapping.)
+__device__ __forceinline__ uint32_t at_stage(uint32_t o, uint32_t k, bool in) {
+  return (o + (in ? k : 0u)) | (in ? 0u : kBufBytes);
+}
 
 // ------------------------------------------------------------------------------ bf16
 // acc[i]: rows 32 i + lane % 32; columns of wave w 32 w + 8 (q / 4) + 4 (lane / 32) + q % 4.
@@ -45,11 +52,11 @@ __device__ __forceinline__ void mainloop_small(const SmallTile& t, int nk, AccSm
   const int arow = (lane & 31) * kBK * 2, brow = kABytes + (32 * w + (lane & 31)) * kBK * 2;
   auto issue = [&](int kt, int slot) {
     lds_char* st = lds + slot * kStageBytes;
-    const uint32_t k = kt < nk ? static_cast<uint32_t>(kt) * (kBK * 2) : kBufBytes;
+    const uint32_t k = static_cast<uint32_t>(kt) * (kBK * 2);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) load_lds16(t.rb, t.ob[i] + k, st + kABytes + (8 * i + w) * 1024);
+    for (int i = 0; i < 4; ++i) load_lds16(t.rb, at_stage(t.ob[i], k, kt < nk), st + kABytes + (8 * i + w) * 1024);
 #pragma unroll
-    for (int i = 0; i < kAL; ++i) load_lds16(t.ra, t.oa[i] + k, st + (8 * i + w) * 1024);
+    for (int i = 0; i < kAL; ++i) load_lds16(t.ra, at_stage(t.oa[i], k, kt < nk), st + (8 * i + w) * 1024);
   };
 #pragma unroll
   for (int s = 0; s + 1 < S; ++s) issue(s, s);
@@ -93,7 +100,7 @@ __device__ __forceinline__ int gemm_mainloop_small(const uint16_t* A, int64_t ld
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int r = 64 * i + 8 * w + lr;
-    if (i < 2) t.oa[i] = static_cast<uint32_t>(min(r, a_rows - 1) * lda * 2 + c16);
+    if (i < 2) t.oa[i] = r < a_rows ? static_cast<uint32_t>(r * lda * 2 + c16) : kBufBytes;
     t.ob[i] = static_cast<uint32_t>(b_row_small(r, b_n0, b_half, swiglu) * ldb * 2 + c16);
   }
 #pragma unroll
@@ -161,118 +168,131 @@ struct MxSmallTile {
   uint32_t sa_grp, sb_grp;    // bytes from one scale group to the next
 };
 
-// Loads of the stages newer than stage kt (position p in its scale group) that are in flight at
-// its boundary: stages kt + 1 .. kt + S - 2, two more in each that opens a scale group.
-constexpr int mx_small_newer(int p, int S, int L) {
+// Loads of the stages newer than stage kt (position p in its scale group of G stages) that are in
+// flight at its boundary: stages kt + 1 .. kt + S - 2, two more in each that opens a scale group.
+constexpr int mx_small_newer(int p, int S, int L, int G) {
   int n = 0;
-  for (int j = p + 1; j <= p + S - 2; ++j) n += L + (j % 4 == 0 ? 2 : 0);
+  for (int j = p + 1; j <= p + S - 2; ++j) n += L + (j % G == 0 ? 2 : 0);
   return n;
 }
 
+// A stage is one whole 128-byte line of every weight row: 128 K elements of E4M3 codes, 256 of
+// E2M1 (with 64-byte stages every E2M1 line was loaded in two halves).
 template <int NI, bool BF4>
 __device__ __forceinline__ void mainloop_mx_small(const MxSmallTile& t, int nk, AccMxSmall& acc, char* lds_raw) {
-  constexpr int kAL = NI <= 2 ? 2 : 4;                    // A loads per wave and stage: 32 rows each
-  constexpr int kBL = BF4 ? 4 : 8;
-  constexpr int kBRow = BF4 ? 64 : 128;                   // B bytes per row and stage
-  constexpr int kABytes = kAL * 32 * 128, kStageBytes = kABytes + kBN * kBRow;
+  constexpr int kW = BF4 ? 2 : 1;                         // 128-element pieces (scale words) per stage
+  constexpr int kG = 4 / kW;                              // stages per scale group
+  constexpr int kAPart = NI * 32 * 128;                   // A bytes of one 128-element piece
+  constexpr int kABytes = kW * kAPart, kStageBytes = kABytes + kBN * 128;
   constexpr int kFit = kMxScaleOff / kStageBytes;
-  constexpr int S = kFit < 5 ? kFit : 5;                  // stages: E4M3 weights 3, E2M1 5 or 4
-  constexpr int kL = kAL + kBL;
-  constexpr int kFmtB = BF4 ? 4 : 0;
   // the group of stage kt + S - 1 goes into the buffer of the group two before it, whose last words
-  // every wave has read before the barrier of stage kt only if S <= 5
-  static_assert(S >= 3 && S <= 5, "scale group buffers");
+  // every wave has read before the barrier of stage kt only if S <= kG + 1
+  constexpr int S = kFit < kG + 1 ? kFit : kG + 1;        // stages: E4M3 weights 4 or 3, E2M1 3 or 2
+  constexpr int kL = NI * kW + 8;                         // loads per wave: A 32 rows, B 32 rows x 128 bytes each
+  constexpr int kFmtB = BF4 ? 4 : 0;
+  static_assert(S >= 2, "stages");
   typedef __attribute__((address_space(3))) v4i_t lds_v4i;
   typedef __attribute__((address_space(3))) uint32_t lds_u32;
   lds_char* const lds = (lds_char*)lds_raw;
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int swz = (lane >> 1) & 7, swz4 = (lane >> 2) & 3, h = lane >> 5;
+  const int swz = (lane >> 1) & 7, h = lane >> 5;
   const uint32_t sel = h ? 0x0C0C0301u : 0x0C0C0200u;     // bytes h and 2 + h of a scale word
-  const int arow = (lane & 31) * 128, brow = kABytes + (64 * w + (lane & 31)) * kBRow;
+  const int arow = (lane & 31) * 128, brow = kABytes + (64 * w + (lane & 31)) * 128;
   const int asc = kMxScaleOff + (lane & 31) * 16, bsc = kMxScaleOff + kBM * 16 + (64 * w + (lane & 31)) * 16;
   // stage kt into `slot`; a stage that opens a scale group also brings the group's 16 bytes per
   // row (A rows 64 (w % 2) + lane: two waves load the same ones; B rows 64 w + lane)
   auto issue = [&](int kt, int slot, auto opens) {
     lds_char* st = lds + slot * kStageBytes;
     const bool in = kt < nk;
-    const uint32_t ka = in ? static_cast<uint32_t>(kt) * 128u : kBufBytes;
-    const uint32_t kb = in ? static_cast<uint32_t>(kt) * kBRow : kBufBytes;
+    const uint32_t k = static_cast<uint32_t>(kt) * 128u;
 #pragma unroll
-    for (int i = 0; i < kBL; ++i) load_lds16(t.rb, t.ob[i] + kb, st + kABytes + (4 * i + w) * 1024);
+    for (int i = 0; i < 8; ++i) load_lds16(t.rb, at_stage(t.ob[i], k, in), st + kABytes + (4 * i + w) * 1024);
 #pragma unroll
-    for (int i = 0; i < kAL; ++i) load_lds16(t.ra, t.oa[i] + ka, st + (4 * i + w) * 1024);
+    for (int c = 0; c < kW; ++c)
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+        load_lds16(t.ra, at_stage(t.oa[i], k * kW + c * 128u, in), st + c * kAPart + (4 * i + w) * 1024);
     if constexpr (decltype(opens)::value) {
-      const uint32_t g = static_cast<uint32_t>(kt) >> 2;
+      const uint32_t g = static_cast<uint32_t>(kt) / kG;
       lds_char* sc = lds + kMxScaleOff + (g & 1) * kMxScaleBuf;
-      load_lds16(t.rsa, in ? t.osa + g * t.sa_grp : kBufBytes, sc + (w & 1) * 1024);
-      load_lds16(t.rsb, in ? t.osb + g * t.sb_grp : kBufBytes, sc + kBM * 16 + w * 1024);
+      load_lds16(t.rsa, at_stage(t.osa, g * t.sa_grp, in), sc + (w & 1) * 1024);
+      load_lds16(t.rsb, at_stage(t.osb, g * t.sb_grp, in), sc + kBM * 16 + w * 1024);
     }
   };
   int slot = 0, fill = S - 1;
   auto stage = [&](int kt, auto pos) {
     constexpr int p = decltype(pos)::value;
-    wait_vm<mx_small_newer(p, S, kL)>();
+    wait_vm<mx_small_newer(p, S, kL, kG)>();
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     const lds_char* st = lds + slot * kStageBytes;
-    const int sg = ((kt >> 2) & 1) * kMxScaleBuf + 4 * p;
-    uint32_t swa[NI], swb[2];
+    const int sg = ((kt / kG) & 1) * kMxScaleBuf + 4 * kW * p;
+    int sa[kW][NI], sb[kW][2];
+    v8i_t a[2 * kW][NI], b[2 * kW][2];
 #pragma unroll
-    for (int i = 0; i < NI; ++i) swa[i] = *(const lds_u32*)(lds + sg + asc + i * 512);
+    for (int c = 0; c < kW; ++c) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j) swb[j] = *(const lds_u32*)(lds + sg + bsc + j * 512);
-    v8i_t a[2][NI], b[2][2];
+      for (int i = 0; i < NI; ++i) sa[c][i] = static_cast<int>(*(const lds_u32*)(lds + sg + 4 * c + asc + i * 512));
+#pragma unroll
+      for (int j = 0; j < 2; ++j) sb[c][j] = static_cast<int>(*(const lds_u32*)(lds + sg + 4 * c + bsc + j * 512));
+    }
     auto frag = [&](int row_off, int kk) {
       const v4i_t lo = *(const lds_v4i*)(st + row_off + (((4 * kk + h) ^ swz) << 4));
       const v4i_t hi = *(const lds_v4i*)(st + row_off + (((4 * kk + 2 + h) ^ swz) << 4));
       return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     };
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
+    for (int kk = 0; kk < 2 * kW; ++kk) {
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        if constexpr (BF4) {
-          const v4i_t v = *(const lds_v4i*)(st + brow + j * 32 * kBRow + (((2 * kk + h) ^ swz4) << 4));
+        if constexpr (BF4) {   // 32 codes per lane: piece 2 kk + h of the line
+          const v4i_t v = *(const lds_v4i*)(st + brow + j * 32 * 128 + (((2 * kk + h) ^ swz) << 4));
           b[kk][j] = __builtin_shufflevector(v, v, 0, 1, 2, 3, -1, -1, -1, -1);
         } else {
-          b[kk][j] = frag(brow + j * 32 * kBRow, kk);
+          b[kk][j] = frag(brow + j * 32 * 128, kk);
         }
       }
 #pragma unroll
-      for (int i = 0; i < NI; ++i) a[kk][i] = frag(arow + i * 32 * 128, kk);
+      for (int i = 0; i < NI; ++i) a[kk][i] = frag((kk >> 1) * kAPart + arow + i * 32 * 128, kk & 1);
     }
     asm volatile("" ::: "memory");
-    issue(kt + S - 1, fill, std::integral_constant<bool, (p + S - 1) % 4 == 0>{});
+    issue(kt + S - 1, fill, std::integral_constant<bool, (p + S - 1) % kG == 0>{});
     fill = slot;
     slot = slot + 1 == S ? 0 : slot + 1;
-    int sa[NI], sb[2];
 #pragma unroll
-    for (int i = 0; i < NI; ++i) sa[i] = static_cast<int>(__builtin_amdgcn_perm(swa[i], swa[i], sel));
+    for (int c = 0; c < kW; ++c) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j) sb[j] = static_cast<int>(__builtin_amdgcn_perm(swb[j], swb[j], sel));
+      for (int i = 0; i < NI; ++i) sa[c][i] = static_cast<int>(__builtin_amdgcn_perm(sa[c][i], sa[c][i], sel));
 #pragma unroll
-    for (int i = 0; i < NI; ++i)
+      for (int j = 0; j < 2; ++j) sb[c][j] = static_cast<int>(__builtin_amdgcn_perm(sb[c][j], sb[c][j], sel));
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(b[0][j], a[0][i], acc[i][j], kFmtB, 0, 0, sb[j], 0, sa[i]);
+      for (int i = 0; i < NI; ++i)
 #pragma unroll
-    for (int i = 0; i < NI; ++i)
+        for (int j = 0; j < 2; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(b[2 * c][j], a[2 * c][i], acc[i][j], kFmtB, 0, 0,
+                                                                      sb[c][j], 0, sa[c][i]);
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(b[1][j], a[1][i], acc[i][j], kFmtB, 0, 1, sb[j], 1, sa[i]);
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(b[2 * c + 1][j], a[2 * c + 1][i], acc[i][j], kFmtB, 0,
+                                                                      1, sb[c][j], 1, sa[c][i]);
+    }
   };
   const std::true_type yes;
   const std::false_type no;
 #pragma unroll
   for (int s = 0; s + 1 < S; ++s) {
-    if (s % 4 == 0) issue(s, s, yes);
+    if (s % kG == 0) issue(s, s, yes);
     else issue(s, s, no);
   }
-  for (int kt = 0; kt < nk; kt += 4) {   // K is a multiple of 512: whole scale groups
+  for (int kt = 0; kt < nk; kt += kG) {   // K is a multiple of 512: whole scale groups
     stage(kt, std::integral_constant<int, 0>{});
     stage(kt + 1, std::integral_constant<int, 1>{});
-    stage(kt + 2, std::integral_constant<int, 2>{});
-    stage(kt + 3, std::integral_constant<int, 3>{});
+    if constexpr (kG == 4) {
+      stage(kt + 2, std::integral_constant<int, 2>{});
+      stage(kt + 3, std::integral_constant<int, 3>{});
+    }
   }
   wait_vm<0>();
 }
@@ -296,18 +316,11 @@ __device__ __forceinline__ int gemm_mainloop_mx_small(const uint8_t* A, int64_t 
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     const int r = 32 * i + 8 * w + lr;
-    if (i < 4) t.oa[i] = static_cast<uint32_t>(min(r, a_rows - 1) * lda + c16);
-    if constexpr (!BF4) t.ob[i] = static_cast<uint32_t>(b_row_map(r, b_n0, b_half, swiglu) * ldb + c16);
+    if (i < 4) t.oa[i] = r < a_rows ? static_cast<uint32_t>(r * lda + c16) : kBufBytes;
+    t.ob[i] = static_cast<uint32_t>(b_row_map(r, b_n0, b_half, swiglu) * ldb + c16);
   }
-  if constexpr (BF4) {
-    const int c4 = ((lane & 3) ^ ((lane >> 4) & 3)) * 16;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int r = 16 * (4 * i + w) + (lane >> 2);
-      t.ob[i] = static_cast<uint32_t>(b_row_map(r, b_n0, b_half, swiglu) * ldb + c4);
-    }
-  }
-  t.osa = static_cast<uint32_t>(min(64 * (w & 1) + lane, a_rows - 1) * a_srow);
+  const int sr = 64 * (w & 1) + lane;
+  t.osa = sr < a_rows ? static_cast<uint32_t>(sr * a_srow) : kBufBytes;
   t.osb = static_cast<uint32_t>(b_row_map(64 * w + lane, b_n0, b_half, swiglu) * b_srow);
   t.sa_grp = static_cast<uint32_t>(a_sgrp);
   t.sb_grp = static_cast<uint32_t>(b_sgrp);
@@ -317,7 +330,7 @@ __device__ __forceinline__ int gemm_mainloop_mx_small(const uint8_t* A, int64_t 
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
-  const int nk = K / 128, ni = __builtin_amdgcn_readfirstlane((a_rows + 31) >> 5);
+  const int nk = K / (BF4 ? 256 : 128), ni = __builtin_amdgcn_readfirstlane((a_rows + 31) >> 5);
   switch (ni) {
     case 1: mainloop_mx_small<1, BF4>(t, nk, acc, lds); break;
     case 2: mainloop_mx_small<2, BF4>(t, nk, acc, lds); break;

@@ -74,6 +74,16 @@ __device__ __forceinline__ void load_lds16(v4i rsrc, uint32_t voff, const lds_ch
   asm volatile("buffer_load_dwordx4 %0, %1, 0 offen lds" :: "v"(voff), "s"(rsrc), "{m0}"(m0v) : "memory");
 }
 
+// A store past the L2 (agent scope, written through to memory): once it has completed (vmcnt), an
+// agent-scope acquire on any XCD sees it, without the release that writes back the whole L2. Not
+// counted by the compiler: the kernel waits with wait_vm.
+__device__ __forceinline__ void store_through16(void* p, u32x4 v) {
+  asm volatile("global_store_dwordx4 %0, %1, off sc1" :: "v"(p), "v"(v) : "memory");
+}
+__device__ __forceinline__ void store_through4(void* p, uint32_t v) {
+  asm volatile("global_store_dword %0, %1, off sc1" :: "v"(p), "v"(v) : "memory");
+}
+
 template <int V>
 __device__ __forceinline__ void wait_vm() {   // s_waitcnt vmcnt(V) only
   static_assert(V >= 0 && V < 64);

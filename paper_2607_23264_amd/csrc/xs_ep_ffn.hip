@@ -6,8 +6,8 @@
 // columns of h each) and P2 = H / 256 Linear-2 tiles (down GEMM whose epilogue stores the
 // output rows into the combine windows of their source ranks: the remote-store bursts of
 // Sec. 4.3). A Linear-2 tile of row p reads the whole h row block, so it waits until all P1
-// Linear-1 tiles of row p have released their stores (per-row counters, agent-scope
-// release/acquire, bounded wait).
+// Linear-1 tiles of row p have stored theirs (per-row counters; stores written through to memory,
+// an agent-scope acquire, a bounded wait).
 //
 // Tile order per persistent workgroup ("scheduler instance" g of G):
 //   BURST       Expert-Wave: global list [L1 of wave 0, L2 of wave 0, L1 of wave 1, ...],
@@ -203,6 +203,17 @@ __device__ __forceinline__ void claim_take(const EpArgs& a, Claim* cl) {
   }
 }
 
+// One Linear-1 tile of row p is done: its h stores went past the L2, and every wave's have
+// completed when the barrier opens, so the count itself needs no release. A release writes back
+// the L2, under every other tile on the XCD too: with one per tile the FFN of the 4096-token share
+// took 2540 us where it takes 2440, and its Linear-1 mainloops 171 us a tile instead of 161.
+__device__ __forceinline__ void count_l1_tile(const EpArgs& a, int p) {
+  wait_vm<0>();
+  __syncthreads();
+  if (threadIdx.x == 0 && p != a.withhold_row)
+    __hip_atomic_fetch_add(&a.l1_done[p], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 __device__ __forceinline__ void ep_l1_tile(const EpArgs& a, int p, int nt, bool fused,
                                            char* lds, char** rowptr, Claim* cl) {
   const int tid = threadIdx.x;
@@ -239,14 +250,11 @@ __device__ __forceinline__ void ep_l1_tile(const EpArgs& a, int p, int nt, bool 
   }
   __syncthreads();
   claim_take(a, cl);
-  store_rows(lds, kEpiPitchH, kBN / 2, rows, rowptr);
   if (fused) {
-    // The workgroup barrier orders every wave's h stores before thread 0's agent-scope
-    // release (one L2 writeback per tile instead of one per wave).
-    __syncthreads();
-    if (tid == 0 && p != a.withhold_row)
-      __hip_atomic_fetch_add(&a.l1_done[p], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    store_rows<true>(lds, kEpiPitchH, kBN / 2, rows, rowptr);
+    count_l1_tile(a, p);
   } else {
+    store_rows(lds, kEpiPitchH, kBN / 2, rows, rowptr);
     lds_barrier();   // the unfused h rows are read by a later launch
   }
   if (a.tr.buf && tid == 0)
@@ -399,7 +407,6 @@ __device__ __forceinline__ void ep_l1_tile_mx(const EpArgs& a, int p, int nt, bo
   const int tid = tid_here();
   __syncthreads();
   claim_take(a, cl);
-  typedef __attribute__((address_space(1))) u32x4 global_u32x4;
   // four rows' LDS reads in flight before their stores
   constexpr int kRowsPerPass = kMxThreads / 8;
 #pragma unroll 1
@@ -418,18 +425,12 @@ __device__ __forceinline__ void ep_l1_tile_mx(const EpArgs& a, int p, int nt, bo
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u)
-      if (dst[u]) *(global_u32x4*)(dst[u] + nt * 128 + pc * 16) = v[u];
+      if (dst[u]) store_through16(dst[u] + nt * 128 + pc * 16, v[u]);
   }
   if (tid < rows)
-    *(__attribute__((address_space(1))) uint32_t*)(a.hs + ((nt >> 2) * a.h_rows + hrow0 + tid) * 16 + (nt & 3) * 4) =
-        *reinterpret_cast<const uint32_t*>(lds + kHqScaleOff + tid * 4);
-  if (fused) {
-    __syncthreads();
-    if (tid == 0 && p != a.withhold_row)
-      __hip_atomic_fetch_add(&a.l1_done[p], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-  } else {
-    lds_barrier();
-  }
+    store_through4(a.hs + ((nt >> 2) * a.h_rows + hrow0 + tid) * 16 + (nt & 3) * 4,
+                   *reinterpret_cast<const uint32_t*>(lds + kHqScaleOff + tid * 4));
+  count_l1_tile(a, p);
   if (a.tr.buf && tid == 0)
     trace_tile(a, 1, static_cast<uint32_t>(p * a.P1 + nt), t0, t1, wall_ticks(), t0, stw,
                static_cast<uint64_t>(rows) * (128 + 4), rows);

@@ -383,7 +383,9 @@ __device__ __forceinline__ void stage_swiglu(const Acc& acc, char* lds) {
 }
 
 // Stores staged rows [0, rows) through the per-row destination pointers in LDS (null rows are
-// skipped). cols = 256 (plain) or 128 (SwiGLU). Every piece is one 128-bit store.
+// skipped). cols = 256 (plain) or 128 (SwiGLU). Every piece is one 128-bit store, with kThrough
+// past the L2.
+template <bool kThrough = false>
 __device__ __forceinline__ void store_rows(const char* lds_bytes, int pitch, int cols, int rows,
                                            char* const* rowptr) {
   typedef __attribute__((address_space(1))) u32x4 global_u32x4;
@@ -401,7 +403,8 @@ __device__ __forceinline__ void store_rows(const char* lds_bytes, int pitch, int
     char* p = rowptr[r];
     if (!p) continue;
     const u32x4 v = *reinterpret_cast<const u32x4*>(lds + r * pitch + pc * 8);
-    *(global_u32x4*)(p + pc * 16) = v;
+    if constexpr (kThrough) store_through16(p + pc * 16, v);
+    else *(global_u32x4*)(p + pc * 16) = v;
   }
 }
 

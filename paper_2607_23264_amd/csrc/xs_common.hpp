@@ -84,6 +84,10 @@ __device__ __forceinline__ void store_through4(void* p, uint32_t v) {
   asm volatile("global_store_dword %0, %1, off sc1" :: "v"(p), "v"(v) : "memory");
 }
 
+// Workgroup barrier for data exchanged in LDS only: global stores may still be in flight
+// (__syncthreads waits until they have reached memory, a microsecond or two each time).
+__device__ __forceinline__ void lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 template <int V>
 __device__ __forceinline__ void wait_vm() {   // s_waitcnt vmcnt(V) only
   static_assert(V >= 0 && V < 64);

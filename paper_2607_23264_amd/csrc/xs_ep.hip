@@ -6,7 +6,8 @@
 // Layout: per 256-token chunk, every wave builds a 64-bit lane mask per expert in LDS
 // (ds_or_b64), so a slot's rank among earlier tokens of the chunk routed to the same expert
 // is a popcount: a deterministic, stable slot assignment. Chunk counts are scanned per
-// source, then across sources and across the experts of each window.
+// source, then across sources and across the experts of each window. A small batch's layout is
+// one workgroup's work.
 // Dispatch: one wavefront per token row; every lane holds 16-byte pieces of the row in
 // registers and stores them, 128-bit and coalesced, into the k destination rows. A row is
 // contiguous on both sides, so no LDS staging is needed to coalesce.
@@ -225,7 +226,10 @@ __global__ __launch_bounds__(256) void route_topk16_kernel(const float* __restri
 constexpr int kChunk = 256;   // tokens per layout chunk (4 waves)
 
 // Per chunk: stable rank of each slot among the chunk's earlier slots of the same expert
-// (written to slot_row as a partial value) and per-expert chunk counts.
+// (written to slot_row as a partial value) and per-expert chunk counts. Up to KMAX slots a token
+// are held in registers (reading the indices again for every comparison took 10.8 us at 4096
+// tokens of 8 sources, k = 8); KMAX 0: any number, from memory.
+template <int KMAX>
 __global__ __launch_bounds__(256) void layout_chunk_kernel(const int* __restrict__ idx, int T,
                                                            int k, int E, int n_chunks,
                                                            int* __restrict__ slot_row,
@@ -240,7 +244,24 @@ __global__ __launch_bounds__(256) void layout_chunk_kernel(const int* __restrict
   const int t = c * kChunk + tid;
   const int64_t base = (static_cast<int64_t>(s) * T + t) * k;
   const unsigned long long bit = 1ull << lane;
-  if (t < T) {
+  int ids[KMAX > 0 ? KMAX : 1];
+  if constexpr (KMAX > 0) {
+    if (t < T) {
+#pragma unroll
+      for (int j = 0; j < KMAX; ++j)
+        if (j < k) ids[j] = idx[base + j];
+      bool bad = false;
+#pragma unroll
+      for (int j = 0; j < KMAX; ++j)
+        if (j < k) {
+          if (ids[j] >= 0 && ids[j] < E) atomicOr(&masks[w * E + ids[j]], bit);
+          else bad = true;
+#pragma unroll
+          for (int i = 0; i < j; ++i) bad |= ids[i] == ids[j];
+        }
+      if (bad) set_status(status, XS_EBADINPUT);
+    }
+  } else if (t < T) {
     for (int j = 0; j < k; ++j) {
       int e = idx[base + j];
       if (e >= 0 && e < E) atomicOr(&masks[w * E + e], bit);
@@ -253,12 +274,18 @@ __global__ __launch_bounds__(256) void layout_chunk_kernel(const int* __restrict
   __syncthreads();
   if (t < T) {
     const unsigned long long below = bit - 1ull;
-    for (int j = 0; j < k; ++j) {
-      int e = idx[base + j];
-      if (e < 0 || e >= E) continue;
+    const auto rank = [&](int j, int e) {
+      if (e < 0 || e >= E) return;
       int r = __popcll(masks[w * E + e] & below);
       for (int ww = 0; ww < w; ++ww) r += __popcll(masks[ww * E + e]);
       slot_row[base + j] = r;
+    };
+    if constexpr (KMAX > 0) {
+#pragma unroll
+      for (int j = 0; j < KMAX; ++j)
+        if (j < k) rank(j, ids[j]);
+    } else {
+      for (int j = 0; j < k; ++j) rank(j, idx[base + j]);
     }
   }
   for (int e = tid; e < E; e += 256) {
@@ -266,6 +293,27 @@ __global__ __launch_bounds__(256) void layout_chunk_kernel(const int* __restrict
     for (int ww = 0; ww < 4; ++ww) n += __popcll(masks[ww * E + e]);
     chunk_cnt[(static_cast<int64_t>(s) * n_chunks + c) * E + e] = n;
   }
+}
+
+// Expert e's rows (`rows`, one expert per thread of a 1024-thread block) -> its offset inside its
+// window, the windows' totals and the capacity check; with plan args the local experts' clipped
+// rows. Returns the offset. Begins and ends without a barrier.
+__device__ __forceinline__ int window_offsets(int rows, int e, int E, int epw, int cap, int* start, int* ws, int* s_m,
+                                              int* __restrict__ expert_offsets, int* __restrict__ dest_counts,
+                                              int* status, const PlanArgs& pa) {
+  int all;
+  const int pre = block_exclusive_scan(rows, ws, all);
+  if (e < E && e % epw == 0) start[e / epw] = pre;
+  lds_sync();
+  if (e >= E) return 0;
+  const int off = pre - start[e / epw];
+  expert_offsets[e] = off;
+  if (pa.meta && e >= pa.e_begin && e < pa.e_begin + pa.n_experts) s_m[e - pa.e_begin] = max(0, min(rows, cap - off));
+  if (e % epw == epw - 1) {
+    dest_counts[e / epw] = off + rows;
+    if (off + rows > cap) set_status(status, XS_ECAPACITY);
+  }
+  return off;
 }
 
 // Per source (one block each): exclusive scan of the chunk counts of every expert, and the
@@ -282,7 +330,7 @@ __global__ __launch_bounds__(1024) void layout_scan_kernel(int* __restrict__ chu
                                                            int* __restrict__ expert_offsets,
                                                            int* __restrict__ dest_counts, int* status,
                                                            int* done, PlanArgs pa) {
-  __shared__ int tot[1024], s_m[1024], s_first[1024], s_rows, s_last;
+  __shared__ int start[XS_MAX_WINDOWS], s_m[1024], s_first[1024], ws[16], s_last;
   const int s = blockIdx.x;
   for (int e = threadIdx.x; e < E; e += blockDim.x) {
     int* col = chunk_cnt + static_cast<int64_t>(s) * n_chunks * E + e;
@@ -313,8 +361,10 @@ __global__ __launch_bounds__(1024) void layout_scan_kernel(int* __restrict__ chu
   }
   __syncthreads();
   if (!s_last) return;
-  for (int e = threadIdx.x; e < E; e += blockDim.x) {
-    int run = 0;
+  // one expert per thread (E <= 1024)
+  const int e = threadIdx.x, epw = E / W;
+  int run = 0;
+  if (e < E) {
     // eight sources' counts in flight at a time (one dependent load per source took longer)
     for (int s0 = 0; s0 < n_src; s0 += 8) {
       int v[8];
@@ -327,24 +377,9 @@ __global__ __launch_bounds__(1024) void layout_scan_kernel(int* __restrict__ chu
         run += v[u];
       }
     }
-    tot[e] = run;
   }
-  __syncthreads();
-  const int epw = E / W;
-  for (int e = threadIdx.x; e < E; e += blockDim.x) {
-    int d0 = (e / epw) * epw, off = 0;
-    for (int x = d0; x < e; ++x) off += tot[x];
-    expert_offsets[e] = off;
-    if (pa.meta && e >= pa.e_begin && e < pa.e_begin + pa.n_experts)
-      s_m[e - pa.e_begin] = max(0, min(tot[e], cap - off));
-  }
-  for (int d = threadIdx.x; d < W; d += blockDim.x) {
-    int n = 0;
-    for (int x = d * epw; x < (d + 1) * epw; ++x) n += tot[x];
-    dest_counts[d] = n;
-    if (n > cap) set_status(status, XS_ECAPACITY);
-  }
-  if (pa.meta) plan_rows(pa, 256, s_m, s_first, &s_rows);
+  window_offsets(run, e, E, epw, cap, start, ws, s_m, expert_offsets, dest_counts, status, pa);
+  if (pa.meta) plan_rows(pa, 256, s_m, s_first, ws);
 }
 
 // Every slot: final row = expert offset + source base + chunk base + rank in chunk;
@@ -371,6 +406,79 @@ __global__ __launch_bounds__(256) void layout_finalize_kernel(
   }
 }
 
+// The whole layout of a small batch (and the FFN plan, with plan args) in one workgroup: the chunk,
+// scan and finalize kernels above are each a few dependent memory round trips behind a launch,
+// and at a decode step's sizes nothing else. A thread per slot. Per (unit of 64 tokens of one source,
+// expert) a 64-bit lane mask in LDS gives the rank inside the unit, and, per expert, a running
+// count over the units in (source, token) order gives everything before it, which is also the row
+// order inside an expert. The fused layer's dispatch launch writes the inverse map. 8 sources of 16
+// tokens, 256 experts, with the FFN plan: chunk 7.9 + scan 10.2 us -> 9.5 us, and 3 us off the
+// dispatch, which looked up the rows' bases.
+constexpr int kSmallUnitExperts = 10240;   // units x experts whose masks and counts fit the LDS (120 KiB)
+constexpr int kSmallSlots = 4096;          // four slots per thread
+
+__global__ __launch_bounds__(1024) void layout_small_kernel(const int* __restrict__ idx, int n_src, int T, int k, int E,
+                                                            int W, int cap, int* __restrict__ expert_counts,
+                                                            int* __restrict__ src_base,
+                                                            int* __restrict__ expert_offsets,
+                                                            int* __restrict__ dest_counts, int* __restrict__ slot_row,
+                                                            int* __restrict__ row_src, int* status, PlanArgs pa) {
+  __shared__ unsigned long long masks[kSmallUnitExperts];
+  __shared__ int before[kSmallUnitExperts];
+  __shared__ int offs[1024], start[XS_MAX_WINDOWS], s_m[1024], s_first[1024], ws[16];
+  const int tid = threadIdx.x;
+  const int per_src = (T + 63) / 64, units = n_src * per_src, epw = E / W, slots = n_src * T * k;
+  int e[4], at[4];                         // a slot's expert, and (unit x E + expert) << 6 | lane
+#pragma unroll
+  for (int q = 0; q < 4; ++q) e[q] = tid + 1024 * q < slots ? idx[tid + 1024 * q] : 0;
+  for (int i = tid; i < units * E; i += 1024) masks[i] = 0ull;
+  lds_sync();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int i = tid + 1024 * q;
+    at[q] = -1;
+    if (i >= slots) continue;
+    const int tok = i / k, s = tok / T, t = tok - s * T;
+    if (e[q] >= 0 && e[q] < E) {
+      const int m = (s * per_src + t / 64) * E + e[q];
+      at[q] = m << 6 | (t & 63);
+      const unsigned long long bit = 1ull << (t & 63);
+      // a token that lists one expert twice would give both slots one row
+      if (atomicOr(&masks[m], bit) & bit) set_status(status, XS_EBADINPUT);
+    } else {
+      set_status(status, XS_EBADINPUT);
+    }
+  }
+  lds_sync();
+  int run = 0;
+  if (tid < E) {
+    for (int s = 0, u = tid; s < n_src; ++s) {
+      const int first = run;
+      for (int c = 0; c < per_src; ++c, u += E) {
+        before[u] = run;
+        run += __popcll(masks[u]);
+      }
+      src_base[static_cast<int64_t>(s) * E + tid] = first;
+      expert_counts[static_cast<int64_t>(s) * E + tid] = run - first;
+    }
+  }
+  const int off = window_offsets(run, tid, E, epw, cap, start, ws, s_m, expert_offsets, dest_counts, status, pa);
+  if (tid < E) offs[tid] = off;
+  lds_sync();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    if (at[q] < 0) continue;
+    const int i = tid + 1024 * q, m = at[q] >> 6;
+    const int r = offs[e[q]] + before[m] + __popcll(masks[m] & ((1ull << (at[q] & 63)) - 1ull));
+    slot_row[i] = r;
+    if (row_src && r < cap) {
+      const int s = i / (T * k);
+      row_src[static_cast<int64_t>(e[q] / epw) * cap + r] = (s << 24) | (i - s * T * k);
+    }
+  }
+  if (pa.meta) plan_rows(pa, 256, s_m, s_first, ws);
+}
+
 // ------------------------------------------------------------------------------ dispatch
 // The rest of the layout, done by the dispatch launch of the fused layer (FinArgs with idx_all
 // set): the dispatch waves compute their own slots' final rows from the scan's bases (and
@@ -384,11 +492,13 @@ __device__ __forceinline__ int final_row(const FinArgs& fa, int E, int s, int t,
          fa.chunk_base[(static_cast<int64_t>(s) * fa.n_chunks + t / kChunk) * E + e] + r;
 }
 
-// One wave per token (measured: a quarter row per wave, four waves per token, is slower).
-// Lanes hold up to 8 16-byte pieces of the row per round and store them into the k
-// destination rows.
+// `parts` waves per token, each a part of its row: one for large batches (with 4096 tokens a
+// quarter row per wave is slower), up to eight for small ones, where a lone wave would issue the k
+// copies of a whole row by itself (16 tokens of 14 KiB, k = 8: 10.8 us with one). Lanes hold up to 8
+// 16-byte pieces of the row per round and store them into the k destination rows. Where the
+// waves also finish the rows (idx_all, not rows_final), one wave per token only.
 __global__ __launch_bounds__(256) void dispatch_kernel(const char* __restrict__ x, int64_t x_stride,
-                                                       int nch, int T,
+                                                       int nch, int T, int parts,
                                                        const int* __restrict__ idx,
                                                        int* __restrict__ slot_row, int k,
                                                        int E, WinSet win, int* status, FinArgs fa) {
@@ -396,26 +506,31 @@ __global__ __launch_bounds__(256) void dispatch_kernel(const char* __restrict__ 
   const int lane = threadIdx.x & 63;
   const int epw = E / win.n;
   if (fa.idx_all && static_cast<int>(blockIdx.x) >= fa.n_disp_blocks) {
-    // finalize the other sources' slots
+    // finalize the other sources' slots (with rows_final every source's, their inverse map only)
     const int64_t per = static_cast<int64_t>(T) * k;
-    const int64_t n = static_cast<int64_t>(fa.n_src - 1) * per;
+    const int64_t n = static_cast<int64_t>(fa.n_src - (fa.rows_final ? 0 : 1)) * per;
     const int64_t step = static_cast<int64_t>(gridDim.x - fa.n_disp_blocks) * blockDim.x;
     for (int64_t i0 = static_cast<int64_t>(blockIdx.x - fa.n_disp_blocks) * blockDim.x + threadIdx.x; i0 < n;
          i0 += step) {
-      const int64_t i = i0 < fa.src * per ? i0 : i0 + per;
+      const int64_t i = fa.rows_final || i0 < fa.src * per ? i0 : i0 + per;
       const int e = fa.idx_all[i];
       if (e < 0 || e >= E) continue;
       const int64_t st = i / k;
       const int j = static_cast<int>(i - st * k);
       const int s = static_cast<int>(st / T);
       const int t = static_cast<int>(st - static_cast<int64_t>(s) * T);
-      const int r = final_row(fa, E, s, t, e, fa.slot_row_all[i]);
-      fa.slot_row_all[i] = r;
+      int r = fa.slot_row_all[i];
+      if (!fa.rows_final) {
+        r = final_row(fa, E, s, t, e, r);
+        fa.slot_row_all[i] = r;
+      }
       if (r < fa.cap) fa.row_src[static_cast<int64_t>(e / epw) * fa.cap + r] = (s << 24) | (t * k + j);
     }
     return;
   }
-  const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int wv = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int t = wv / parts, part = wv - t * parts;
+  const int per = (nch + parts - 1) / parts, c_begin = part * per, c_end = min(nch, c_begin + per);
   // lane j < k resolves destination j; broadcast below with readlane
   char* my_dst = nullptr;
   if (t < T && lane < k) {
@@ -425,7 +540,7 @@ __global__ __launch_bounds__(256) void dispatch_kernel(const char* __restrict__ 
     if (e < 0 || e >= E) {
       set_status(status, XS_EBADINPUT);
     } else {
-      if (fa.idx_all) {
+      if (fa.idx_all && !fa.rows_final) {
         r = final_row(fa, E, fa.src, t, e, r);
         slot_row[si] = r;
         if (r < fa.cap) fa.row_src[static_cast<int64_t>(e / epw) * fa.cap + r] = (fa.src << 24) | (t * k + lane);
@@ -437,12 +552,12 @@ __global__ __launch_bounds__(256) void dispatch_kernel(const char* __restrict__ 
   }
   if (t < T) {
     const u32x4* src = reinterpret_cast<const u32x4*>(x + static_cast<int64_t>(t) * x_stride);
-    for (int c0 = 0; c0 < nch; c0 += 64 * 8) {
+    for (int c0 = c_begin; c0 < c_end; c0 += 64 * 8) {
       u32x4 v[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         int c = c0 + u * 64 + lane;
-        if (c < nch) v[u] = src[c];
+        if (c < c_end) v[u] = src[c];
       }
       for (int j = 0; j < k; ++j) {
         uint64_t p = __shfl(reinterpret_cast<uint64_t>(my_dst), j);
@@ -451,7 +566,7 @@ __global__ __launch_bounds__(256) void dispatch_kernel(const char* __restrict__ 
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
           int c = c0 + u * 64 + lane;
-          if (c < nch) dst[c] = v[u];   // (measured: nontemporal stores here are slower)
+          if (c < c_end) dst[c] = v[u];   // (measured: nontemporal stores here are slower)
         }
       }
     }
@@ -476,18 +591,19 @@ __global__ __launch_bounds__(256) void dispatch_kernel(const char* __restrict__ 
 __global__ __launch_bounds__(256) void combine_reduce_kernel(const char* __restrict__ cbuf,
                                                              int64_t cstride,
                                                              const float* __restrict__ w, int T,
-                                                             int k, int H,
+                                                             int k, int H, int parts,
                                                              uint16_t* __restrict__ out) {
   const int lane = threadIdx.x & 63;
-  // four waves per token, each over a quarter of the row's 16-byte pieces (one wave per
-  // token left 16 waves per CU at T = 4096, too few loads in flight to stream HBM)
+  // `parts` waves per token, each over a part of the row's 16-byte pieces: four for large batches
+  // (one wave per token left 16 waves per CU at T = 4096, too few loads in flight to stream HBM),
+  // for small ones as many as leave each a single pass
   const int wv = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int t = wv >> 2;
+  const int t = wv / parts;
   if (t >= T) return;
   const float wl = lane < k ? w[static_cast<int64_t>(t) * k + lane] : 0.f;
   const int nch = H >> 3;
-  const int per = (nch + 3) >> 2;
-  const int c_begin = (wv & 3) * per;
+  const int per = (nch + parts - 1) / parts;
+  const int c_begin = (wv - t * parts) * per;
   const int c_end = min(nch, c_begin + per);
   u32x4* dst = reinterpret_cast<u32x4*>(out + static_cast<int64_t>(t) * H);
   const char* rows = cbuf + static_cast<int64_t>(t) * k * cstride;
@@ -620,6 +736,12 @@ extern "C" int xs_dispatch_layout_workspace_bytes(int32_t n_src, int32_t T, int3
 }
 
 namespace xs_host {
+// Whether one workgroup lays the batch out: its units' masks fit the LDS, its slots the threads.
+bool layout_is_small(int32_t n_src, int32_t T, int32_t k, int32_t E) {
+  const int64_t units = n_src * ((static_cast<int64_t>(T) + 63) / 64);
+  return static_cast<int64_t>(n_src) * T * k <= kSmallSlots && units * E <= kSmallUnitExperts;
+}
+
 int dispatch_layout(const int32_t* topk_idx, int32_t n_src, int32_t T, int32_t k, int32_t E,
                     int32_t W, int32_t cap, int32_t* expert_counts, int32_t* src_base,
                     int32_t* expert_offsets, int32_t* dest_counts, int32_t* slot_row,
@@ -632,13 +754,20 @@ int dispatch_layout(const int32_t* topk_idx, int32_t n_src, int32_t T, int32_t k
       W > XS_MAX_WINDOWS || E % W || cap < 0 || static_cast<int64_t>(T) * k >= (1 << 24))
     return XS_EINVAL;
   if (!workspace || workspace_bytes < layout_ws_bytes(n_src, T, E)) return XS_EWORKSPACE;
+  if (layout_is_small(n_src, T, k, E)) {
+    // with a plan (the fused layer), the dispatch launch writes the inverse map
+    hipLaunchKernelGGL(layout_small_kernel, dim3(1), dim3(1024), 0, st, topk_idx, n_src, T, k, E, W, cap, expert_counts,
+                       src_base, expert_offsets, dest_counts, slot_row, plan ? nullptr : row_src, dev_status,
+                       plan ? *plan : PlanArgs{});
+    return launch_status();
+  }
   const int n_chunks = (T + kChunk - 1) / kChunk;
   int* chunk = static_cast<int*>(workspace);
   int* scan_done = reinterpret_cast<int*>(static_cast<char*>(workspace) + layout_chunk_bytes(n_src, T, E));
   if (n_chunks > 0) {
-    hipLaunchKernelGGL(layout_chunk_kernel, dim3(n_chunks, n_src), dim3(256),
-                       4 * E * sizeof(unsigned long long), st, topk_idx, T, k, E, n_chunks,
-                       slot_row, chunk, dev_status, scan_done);
+    const auto kernel = k <= 8 ? layout_chunk_kernel<8> : (k <= 32 ? layout_chunk_kernel<32> : layout_chunk_kernel<0>);
+    hipLaunchKernelGGL(kernel, dim3(n_chunks, n_src), dim3(256), 4 * E * sizeof(unsigned long long), st, topk_idx, T, k, E,
+                       n_chunks, slot_row, chunk, dev_status, scan_done);
   } else {
     hipLaunchKernelGGL(zero_int_kernel, dim3(1), dim3(1), 0, st, scan_done);
   }
@@ -666,12 +795,14 @@ int dispatch_rows(const void* x, int64_t x_stride, int32_t row_bytes, int32_t T,
                   const int32_t* topk_idx, const int32_t* slot_row, int32_t k, int32_t E,
                   const WinSet& ws, int32_t* dev_status, hipStream_t st, const FinArgs* fin) {
   FinArgs fa{};
-  const int nd = (T + 3) / 4;
+  if (fin) fa = *fin;
+  const int nch = row_bytes / 16;
+  const int parts = (fa.idx_all && !fa.rows_final) || T < 1 ? 1 : std::max(1, std::min({8, 1024 / T, nch / 64}));
+  const int nd = static_cast<int>((static_cast<int64_t>(T) * parts + 3) / 4);
   int nf = 0;
   if (fin) {
-    fa = *fin;
     fa.n_disp_blocks = nd;
-    const int64_t n_other = static_cast<int64_t>(fa.n_src - 1) * T * k;
+    const int64_t n_other = static_cast<int64_t>(fa.n_src - (fa.rows_final ? 0 : 1)) * T * k;
     nf = static_cast<int>(std::min<int64_t>((n_other + 255) / 256, 4096));
     bool any = false;
     for (int d = 0; d < ws.n; ++d) any |= ws.flag[d] != nullptr;
@@ -679,7 +810,7 @@ int dispatch_rows(const void* x, int64_t x_stride, int32_t row_bytes, int32_t T,
   }
   if (nd + nf > 0) {
     hipLaunchKernelGGL(dispatch_kernel, dim3(nd + nf), dim3(256), 0, st, static_cast<const char*>(x),
-                       x_stride, row_bytes / 16, T, topk_idx, const_cast<int32_t*>(slot_row), k, E, ws,
+                       x_stride, nch, T, parts, topk_idx, const_cast<int32_t*>(slot_row), k, E, ws,
                        dev_status, fa);
     if (launch_status()) return XS_EHIP;
   }
@@ -695,8 +826,10 @@ int dispatch(const void* x, int32_t T, int32_t H, const int32_t* topk_idx, const
 int combine_reduce(const void* cbuf, int64_t cstride, const float* w, int32_t T, int32_t k,
                    int32_t H, void* out, hipStream_t st) {
   if (T == 0) return XS_OK;
-  hipLaunchKernelGGL(combine_reduce_kernel, dim3(T), dim3(256), 0, st,
-                     static_cast<const char*>(cbuf), cstride, w, T, k, H,
+  const int parts = T >= 1024 ? 4 : std::max(1, std::min(16, (H / 8 + 127) / 128));
+  const int64_t blocks = (static_cast<int64_t>(T) * parts + 3) / 4;
+  hipLaunchKernelGGL(combine_reduce_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st,
+                     static_cast<const char*>(cbuf), cstride, w, T, k, H, parts,
                      static_cast<uint16_t*>(out));
   return launch_status();
 }

@@ -76,7 +76,7 @@ __global__ __launch_bounds__(1024) void ep_plan_kernel(const int* __restrict__ e
                                                        int n_src, int E,
                                                        const int* __restrict__ expert_offsets,
                                                        PlanArgs pa) {
-  __shared__ int s_m[1024], s_first[1024], s_rows;
+  __shared__ int s_m[1024], s_first[1024], ws[16];
   const int i = threadIdx.x;
   if (i < pa.n_experts) {
     const int e = pa.e_begin + i;
@@ -92,7 +92,7 @@ __global__ __launch_bounds__(1024) void ep_plan_kernel(const int* __restrict__ e
     }
     s_m[i] = max(0, min(m, pa.cap - off));
   }
-  plan_rows(pa, kBM, s_m, s_first, &s_rows);
+  plan_rows(pa, kBM, s_m, s_first, ws);
 }
 
 // Rows [m0, m0 + rows) of local expert x covered by scheduler row p. The expert's m rows fall
@@ -802,6 +802,7 @@ int dispatch_rows(const void*, int64_t, int32_t, int32_t, const int32_t*, const 
                   int32_t, const WinSet&, int32_t*, hipStream_t, const FinArgs*);
 int dispatch(const void*, int32_t, int32_t, const int32_t*, const int32_t*, int32_t, int32_t,
              const WinSet&, int32_t*, hipStream_t);
+bool layout_is_small(int32_t n_src, int32_t T, int32_t k, int32_t E);
 int combine_reduce(const void*, int64_t, const float*, int32_t, int32_t, int32_t, void*,
                    hipStream_t);
 int signal_windows(const WinSet&, hipStream_t);
@@ -1181,7 +1182,8 @@ static int fused_ep_layer(const xs_ep_layer* L, const xs_pacing* pacing, const x
                                 L->slot_row, L->row_src, layout_ws, w.layout_bytes, dev_status, st, &pa);
   if (rc) return rc;
   const int64_t so = static_cast<int64_t>(L->src) * L->T * L->k;
-  const FinArgs fin{L->src, L->n_src, L->cap, (L->T + 255) / 256, 0, L->topk_idx, L->slot_row,
+  const int rows_final = xs_host::layout_is_small(L->n_src, L->T, L->k, L->E);
+  const FinArgs fin{L->src, L->n_src, L->cap, (L->T + 255) / 256, 0, L->topk_idx, rows_final, L->slot_row,
                     reinterpret_cast<const int*>(layout_ws), L->src_base, L->expert_offsets, L->row_src,
                     const_cast<int*>(a.meta) + 11};
   if ((rc = record_event(L, XS_EV_DISPATCH, st))) return rc;

@@ -194,7 +194,7 @@ __device__ __forceinline__ void mainloop_mx_small(const MxSmallTile& t, int nk, 
   typedef __attribute__((address_space(3))) v4i_t lds_v4i;
   typedef __attribute__((address_space(3))) uint32_t lds_u32;
   lds_char* const lds = (lds_char*)lds_raw;
-  const int lane = threadIdx.x & 63;
+  const int lane = lane_id_here();   // not held across other tiles (the 256-row core needs every register)
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int swz = (lane >> 1) & 7, h = lane >> 5;
   const uint32_t sel = h ? 0x0C0C0301u : 0x0C0C0200u;     // bytes h and 2 + h of a scale word

@@ -109,8 +109,13 @@ def _idx_random(n_src, T, k, E, seed):
     return np.argsort(g.random((n_src, T, E)), axis=2)[:, :, :k].astype(np.int32)
 
 
+# (the last rows: the one-workgroup layout at its edges, in slots and in units of 64 tokens times
+# experts, and just past them)
 @pytest.mark.parametrize("n_src,T,k,E,W", [(1, 256, 2, 8, 4), (3, 300, 3, 12, 3), (8, 4096, 8, 256, 8),
-                                           (2, 1, 1, 4, 2), (1, 257, 8, 1024, 64)])
+                                           (2, 1, 1, 4, 2), (1, 257, 8, 1024, 64), (64, 16, 4, 160, 32),
+                                           (65, 15, 4, 160, 32), (1, 128, 32, 1024, 2), (1, 129, 32, 1024, 2),
+                                           (10, 50, 8, 1024, 64), (1, 4096, 1, 16, 16), (1, 4097, 1, 16, 16),
+                                           (3, 20, 33, 64, 4)])
 def test_layout_matches_oracle(n_src, T, k, E, W):
     idx = _idx_random(n_src, T, k, E, seed=T + E)
     cap = n_src * T * k

@@ -91,7 +91,7 @@ __device__ __forceinline__ void trace_tile(const xs_trace& tr, int kind, int til
 
 // Head-group destination of output element (m, col); col is a multiple of 8.
 __device__ __forceinline__ char* head_group_dst(const WinSet& win, const ScatterArgs& sa, int M,
-                                                int m, int col) {
+                                                int m, int col, int64_t* stride = nullptr) {
   const int per_proj = sa.n_heads * sa.head_dim;
   const int p = col / per_proj;
   const int rem = col - p * per_proj;
@@ -99,10 +99,11 @@ __device__ __forceinline__ char* head_group_dst(const WinSet& win, const Scatter
   const int dd = rem - head * sa.head_dim;
   const int g = head / sa.hpg, lh = head - g * sa.hpg;
   const int64_t row = (static_cast<int64_t>(p) * sa.hpg + lh) * M + m;
+  if (stride) *stride = win.stride[g];
   return win.base[g] + row * win.stride[g] + dd * 2;
 }
 
-template <int KIND>
+template <int KIND, int BN>
 __global__ __launch_bounds__(kThreads, 1) void gemm_tiles_kernel(
     const uint16_t* __restrict__ A, int64_t lda, const uint16_t* __restrict__ B, int64_t ldb,
     char* __restrict__ C, int64_t ldc_bytes, int M, int N, int K, ScatterArgs sa, WinSet win,
@@ -111,7 +112,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_tiles_kernel(
   char* lds = smem;
   char** rowptr = reinterpret_cast<char**>(smem + kLdsRowPtrOff);
   const int tid = threadIdx.x;
-  const int tm = (M + kBM - 1) / kBM, tn = N / kBN, ntiles = tm * tn;
+  const int tm = (M + kBM - 1) / kBM, tn = N / BN, ntiles = tm * tn;
   const int G = gridDim.x;
   for (int t = xcd_instance(blockIdx.x, G); t < ntiles; t += G) {
     int mb, nb;
@@ -119,11 +120,11 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_tiles_kernel(
       paced_tile(sa, KIND == KIND_HEAD_GROUP, t, tm, ntiles, &mb, &nb);
     else
       grouped_tile(t, tm, tn, &mb, &nb);
-    const int m0 = mb * kBM, n0 = nb * kBN;
+    const int m0 = mb * kBM, n0 = nb * BN;
     const int rows = min(kBM, M - m0);
     const uint64_t t0 = tr.buf ? wall_ticks() : 0;
-    Acc acc;
-    gemm_mainloop(A + static_cast<int64_t>(m0) * lda, lda, rows, B, ldb, n0, 0, false, K, acc, lds);
+    typename TileShape<BN>::AccT acc;
+    gemm_mainloop<false, BN>(A + static_cast<int64_t>(m0) * lda, lda, rows, B, ldb, n0, 0, false, K, acc, lds);
     const uint64_t t1 = tr.buf ? wall_ticks() : 0;
     if (KIND != KIND_HEAD_GROUP && tid < rows) {
       const int m = m0 + tid;
@@ -137,10 +138,11 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_tiles_kernel(
       }
       rowptr[tid] = p;
     }
-    stage_tile(acc, lds);
+    stage_tile<BN>(acc, lds);
     __syncthreads();
+    constexpr int kPitch = TileShape<BN>::kPitch;
     if (KIND == KIND_HEAD_GROUP) {
-      if (sa.group_aligned) {
+      if (BN == kBN && sa.group_aligned) {
         // The tile's columns are heads [head0, head0 + 256 / head_dim) of one projection and
         // one group: store head by head, consecutive lanes on consecutive 16-byte pieces of
         // consecutive rows, which are contiguous in a head plane (a wave stores 1 KiB runs).
@@ -174,14 +176,30 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_tiles_kernel(
           }
         }
       } else {
-        const int pc = tid & 31;
-        for (int r = tid >> 5; r < rows; r += kThreads / 32) {
-          u32x4 v = *reinterpret_cast<const u32x4*>(lds + (r * kEpiPitch + pc * 8) * 2);
-          *reinterpret_cast<u32x4*>(head_group_dst(win, sa, M, m0 + r, n0 + pc * 8)) = v;
+        // each thread keeps one 8-column piece: its window, plane and row stride are resolved once
+        // (head_dim is a multiple of 8, so a piece lies in one head)
+        constexpr int kPieces = BN / 8, kRowsPass = kThreads / kPieces, U = BN == kBN ? 1 : 4;
+        typedef __attribute__((address_space(1))) u32x4 global_u32x4;
+        const int pc = tid % kPieces, r0 = tid / kPieces;
+        if (r0 < kRowsPass) {
+          int64_t stride;
+          char* dst = head_group_dst(win, sa, M, m0, n0 + pc * 8, &stride);
+          const char* src = lds + pc * 16;
+#pragma unroll 1
+          for (int r = r0; r < rows; r += U * kRowsPass) {
+            u32x4 v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+              if (r + u * kRowsPass < rows) v[u] = *reinterpret_cast<const u32x4*>(src + (r + u * kRowsPass) * kPitch * 2);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+              if (r + u * kRowsPass < rows)
+                *(global_u32x4*)(dst + static_cast<int64_t>(r + u * kRowsPass) * stride) = v[u];
+          }
         }
       }
     } else {
-      store_rows(lds, kEpiPitch, kBN, rows, rowptr);
+      store_rows(lds, kPitch, BN, rows, rowptr);
     }
     lds_barrier();   // output tiles are read only after the kernel
     if (tr.buf && tid == 0) trace_tile(tr, 3, t, t0, t1, wall_ticks());
@@ -331,13 +349,54 @@ static xs_trace trace_or_empty(const xs_trace* t) {
   return *t;
 }
 
+namespace {
+
+// Columns of the output tiles, and what the launch costs in rounds of 256 x 256 tiles over the CUs:
+// 192 or 128 where they leave fewer CUs idle. A 192-column tile takes up to kTile192 of the time of
+// a 256-column one, a 128-column tile up to kTile128 (0.56 to 0.82: its waves read more LDS per
+// MFMA). Measured, 256 / 192 / 128 columns (us): 1000 x 12288 x 4096 95 / 91 / 121, 4096 x 6144 x
+// 2048 109 / 92 / 99, 2048 x 4096 x 4096 78 / - / 64, 300 x 12288 x 4096 74 / 62 / 50, 8192 x 8192 x
+// 1024 125 / - / 143.
+constexpr double kTile192 = 0.87, kTile128 = 0.72;
+
+double tile_rounds(int M, int N, int* columns) {
+  const int64_t cus = xs_host::persistent_grid(0), tm = (M + kBM - 1) / kBM;
+  const auto rounds = [&](int bn) { return static_cast<double>((tm * (N / bn) + cus - 1) / cus); };
+  double best = rounds(256);
+  *columns = 256;
+  if (N % 192 == 0 && rounds(192) * kTile192 < best) {
+    best = rounds(192) * kTile192;
+    *columns = 192;
+  }
+  if (rounds(128) * kTile128 < best) {
+    best = rounds(128) * kTile128;
+    *columns = 128;
+  }
+  return best;
+}
+
+template <int KIND>
+void launch_tiles(int bn, int max_producers, hipStream_t st, const void* a, int64_t lda, const void* b, int64_t ldb,
+                  char* c, int64_t ldc_bytes, int M, int N, int K, const ScatterArgs& sa, const WinSet& ws,
+                  const xs_trace& tr) {
+  const int tiles = ((M + kBM - 1) / kBM) * (N / bn);
+  const int grid = std::min(tiles, xs_host::persistent_grid(max_producers));
+  const auto kernel = bn == 256   ? gemm_tiles_kernel<KIND, 256>
+                      : bn == 192 ? gemm_tiles_kernel<KIND, 192>
+                                  : gemm_tiles_kernel<KIND, 128>;
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), 0, st, static_cast<const uint16_t*>(a), lda,
+                     static_cast<const uint16_t*>(b), ldb, c, ldc_bytes, M, N, K, sa, ws, tr);
+}
+
+}  // namespace
+
 // Split-K launches of the plain GEMM (xs_gemm_skinny.hpp). A form of NB x NJ blocks of 16 x 16
 // costs about kSplitFixed + rounds (NB + NJ) 32 K / kSplitRate, its rounds of workgroups over the
-// CUs each streaming its operand panels at the rate of a CU's memory path; the 256 x 256 tiles
-// cost about kTileFixed + rounds K kTilePerK (half-empty tiles, M <= 128, kTilePerKHalf: they wait
+// CUs each streaming its operand panels at the rate of a CU's memory path; the tiles
+// cost about kTileFixed + tile_rounds K kTilePerK (half-empty tiles, M <= 128, kTilePerKHalf: they wait
 // for loads rather than for MFMAs). The cheapest wins. Measured, tiles -> split (us): 24 x 4096 x
 // 7168 80 -> 11, 256 x 4096 x 7168 120 -> 24, 512 x 8192 x 4096 71 -> 52, 2048 x 2048 x 2048
-// 40 -> 28; 2048 x 4096 x 4096 stays with the tiles (73, against about 105).
+// 40 -> 28; 2048 x 4096 x 4096 stays with the tiles (64, against about 105).
 namespace {
 
 constexpr double kSplitFixed = 2.5, kSplitRate = 75e3;                         // us, bytes per us
@@ -358,8 +417,8 @@ bool gemm_split(const void* a, int64_t lda, const void* b, int64_t ldb, void* c,
       lda > (1 << 23) || ldb > (1 << 23))
     return false;
   const int cus = xs_host::persistent_grid(0);
-  const int tiles = ((M + kBM - 1) / kBM) * (N / kBN);
-  double best = kTileFixed + static_cast<double>((tiles + cus - 1) / cus) * K * (M <= kBM / 2 ? kTilePerKHalf : kTilePerK);
+  int columns;
+  double best = kTileFixed + tile_rounds(M, N, &columns) * K * (M <= kBM / 2 ? kTilePerKHalf : kTilePerK);
   constexpr int forms[6][2] = {{1, 1}, {2, 1}, {2, 2}, {2, 4}, {4, 2}, {4, 4}};
   int form = -1;
   int64_t form_wgs = 0;
@@ -404,13 +463,10 @@ extern "C" int xs_gemm(const void* a, int64_t lda, const void* b, int64_t ldb, v
     return xs_host::launch_status();
   WinSet none{};
   none.n = 0;
-  ScatterArgs sa{};
-  const int tiles = ((M + kBM - 1) / kBM) * (N / kBN);
-  const int grid = std::min(tiles, xs_host::persistent_grid(0));
-  hipLaunchKernelGGL(gemm_tiles_kernel<KIND_PLAIN>, dim3(grid), dim3(kThreads), 0,
-                     static_cast<hipStream_t>(stream), static_cast<const uint16_t*>(a), lda,
-                     static_cast<const uint16_t*>(b), ldb, static_cast<char*>(c), ldc * 2, M, N,
-                     K, sa, none, tr);
+  int bn = kBN;
+  if (!tr.buf) tile_rounds(M, N, &bn);
+  launch_tiles<KIND_PLAIN>(bn, 0, static_cast<hipStream_t>(stream), a, lda, b, ldb,
+                           static_cast<char*>(c), ldc * 2, M, N, K, ScatterArgs{}, none, tr);
   return xs_host::launch_status();
 }
 
@@ -486,16 +542,14 @@ extern "C" int xs_gemm_scatter(const void* a, int64_t lda, const void* b, int64_
   }
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (M > 0) {
-    const int tiles = ((M + kBM - 1) / kBM) * (N / kBN);
-    const int grid = std::min(tiles, xs_host::persistent_grid(max_producers));
+    // a pacing order and a trace are of 256 x 256 tiles
+    const xs_trace tr = trace_or_empty(trace);
+    int bn = kBN;
+    if (!pacing && !tr.buf) tile_rounds(M, N, &bn);
     if (kind == KIND_ROW_BLOCK)
-      hipLaunchKernelGGL(gemm_tiles_kernel<KIND_ROW_BLOCK>, dim3(grid), dim3(kThreads), 0, st,
-                         static_cast<const uint16_t*>(a), lda, static_cast<const uint16_t*>(b), ldb,
-                         nullptr, 0, M, N, K, sa, ws, trace_or_empty(trace));
+      launch_tiles<KIND_ROW_BLOCK>(bn, max_producers, st, a, lda, b, ldb, nullptr, 0, M, N, K, sa, ws, tr);
     else
-      hipLaunchKernelGGL(gemm_tiles_kernel<KIND_HEAD_GROUP>, dim3(grid), dim3(kThreads), 0, st,
-                         static_cast<const uint16_t*>(a), lda, static_cast<const uint16_t*>(b), ldb,
-                         nullptr, 0, M, N, K, sa, ws, trace_or_empty(trace));
+      launch_tiles<KIND_HEAD_GROUP>(bn, max_producers, st, a, lda, b, ldb, nullptr, 0, M, N, K, sa, ws, tr);
     if (xs_host::launch_status()) return XS_EHIP;
   }
   return xs_host::signal_windows(ws, st);

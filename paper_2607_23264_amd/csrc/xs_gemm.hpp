@@ -63,16 +63,20 @@ __device__ __forceinline__ int b_row_map(int r, int n0, int half, bool swiglu) {
   return swiglu ? n0 + ((r >> 5) & 1) * half + (r >> 6) * 32 + (r & 31) : n0 + r;
 }
 
-typedef f32x16 Acc[4][2];
-
-__device__ __forceinline__ void zero_acc(Acc& acc) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
-}
+// Output tiles are 256 x BN, BN = 256, or 192 or 128 where those fill the CUs better: eight waves as
+// kWM x kWN, each kNI x kNJ blocks of 32 x 32 (BN 256: 2 x 4 waves of 128 x 64; BN 192: 4 x 2 of 64 x
+// 96; BN 128: 4 x 2 of 64 x 64). B stages hold BN rows. Every shape adds the same products by the
+// same MFMAs in the same K order, so an output's bits do not depend on it.
+template <int BN>
+struct TileShape {
+  static constexpr int kWN = BN == 256 ? 4 : 2, kWM = 8 / kWN;
+  static constexpr int kNI = kBM / kWM / 32, kNJ = BN / kWN / 32;
+  static constexpr int kBL = BN / 64;                 // direct loads of B per wave and stage
+  static constexpr int kBStage = BN * kBK * 2;        // bytes of a B stage
+  static constexpr int kPitch = BN + 8;               // bf16 per staged output row
+  typedef f32x16 AccT[kNI][kNJ];
+};
+typedef TileShape<kBN>::AccT Acc;
 
 // s_waitcnt vmcnt(0) only (expcnt and lgkmcnt left at their maxima).
 __device__ __forceinline__ void wait_vm0() { __builtin_amdgcn_s_waitcnt(0x0F70); }
@@ -89,7 +93,7 @@ __device__ __forceinline__ void lds_barrier() {
 struct TileAddr {
   const char* a;          // A tile base (row 0, k 0)
   const char* b;          // B base
-  uint32_t oa[4], ob[4];  // per-lane byte offsets of the four direct loads of each operand
+  uint32_t oa[4], ob[4];  // per-lane byte offsets of the (up to four) direct loads of each operand
   int arow, brow;         // LDS byte offsets of this lane's fragment rows (A, B)
   int w;                  // wave index (uniform)
 };
@@ -112,8 +116,9 @@ struct TileAddr {
 // faster, plain GEMMs with K of 7168 or more 0-1.5 % slower (where every CU streams weights at
 // once and the longer lead pays), K = 1024 unchanged; the EP kernels use it, the plain and
 // scatter GEMMs do not. Output is bit-identical either way.
-template <int NI, bool kLateB>
-__device__ __forceinline__ void mainloop_ni(const TileAddr& ta, int nk, Acc& acc, char* lds) {
+template <int BN, int NI, bool kLateB>
+__device__ __forceinline__ void mainloop_ni(const TileAddr& ta, int nk, typename TileShape<BN>::AccT& acc, char* lds) {
+  constexpr int NJ = TileShape<BN>::kNJ, kBL = TileShape<BN>::kBL, kBStage = TileShape<BN>::kBStage;
   const int lane = threadIdx.x & 63;
   const int w = ta.w;
   const int swz = (lane >> 1) & 7;
@@ -127,14 +132,14 @@ __device__ __forceinline__ void mainloop_ni(const TileAddr& ta, int nk, Acc& acc
                                        16, 0, 0);
   };
   auto issue_b = [&](int kt, int slot) {
-    char* st = lds + kBBase + slot * kOpBytes;
+    char* st = lds + kBBase + slot * kBStage;
     const char* b0 = ta.b + kt * kBK * 2;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < kBL; ++i)
       __builtin_amdgcn_global_load_lds((glob_void*)(b0 + ta.ob[i]), (lds_void*)(st + (8 * i + w) * 1024),
                                        16, 0, 0);
   };
-  bf16x8 af[2][4], bfr[2][2];
+  bf16x8 af[2][TileShape<BN>::kNI], bfr[2][NJ];
   auto frags = [&](const char* ca, const char* cb, int kk, int buf) {
     if (NI == 0) return;
     const int piece = (((kk * 2 + khalf) ^ swz) << 4);
@@ -142,26 +147,19 @@ __device__ __forceinline__ void mainloop_ni(const TileAddr& ta, int nk, Acc& acc
     for (int i = 0; i < NI; ++i)
       af[buf][i] = *reinterpret_cast<const bf16x8*>(ca + ta.arow + i * 32 * kBK * 2 + piece);
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < NJ; ++j)
       bfr[buf][j] = *reinterpret_cast<const bf16x8*>(cb + ta.brow + j * 32 * kBK * 2 + piece);
   };
-  auto mma = [&](int buf, int i0, int i1) {
-#pragma unroll
-    for (int i = i0; i < i1; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[buf][j], af[buf][i], acc[i][j], 0, 0, 0);
-  };
-  // per sub-step: 2 NI MFMAs and NI + 2 fragment reads
-  constexpr int kReads = NI + 2, kMfma = 2 * NI;
+  // per sub-step: NJ NI MFMAs and NI + NJ fragment reads
+  constexpr int kReads = NI + NJ, kMfma = NJ * NI;
   // Issue order: A(0), B(0), B(1) | A(1), B(2) | A(2), B(3) | ... At the boundary into
-  // stage s + 1 the loads newer than A(s + 1) are only B(s + 2) (4 per wave), so waiting for
-  // stage s + 1 is vmcnt(4), or vmcnt(0) when B(s + 2) does not exist.
+  // stage s + 1 the loads newer than A(s + 1) are only B(s + 2) (kBL per wave), so waiting for
+  // stage s + 1 is vmcnt(kBL), or vmcnt(0) when B(s + 2) does not exist.
   issue_a(0);
   issue_b(0, 0);
   if (nk > 1) {
     issue_b(1, 1);
-    __builtin_amdgcn_s_waitcnt(0x0F74);   // vmcnt(4): A(0) and B(0) have landed
+    __builtin_amdgcn_s_waitcnt(0x0F70 | kBL);   // vmcnt(kBL): A(0) and B(0) have landed
   } else {
     wait_vm0();
   }
@@ -170,19 +168,19 @@ __device__ __forceinline__ void mainloop_ni(const TileAddr& ta, int nk, Acc& acc
   if (!kLateB && nk > 2) issue_b(2, 2);
   frags(lds, lds + kBBase, 0, 0);
   // One stage. NEXT: a stage follows; IA: A(kt + 2) exists (then B(kt + 2) is the only newer
-  // load at the boundary: vmcnt(4)); IB: B(kt + 3) exists. Compile-time, so the steady loop
+  // load at the boundary: vmcnt(kBL)); IB: B(kt + 3) exists. Compile-time, so the steady loop
   // body is one basic block: with the boundary's conditions inside the loop the register
   // allocator split the accumulators' live ranges and copied all of them every stage.
-  // one fragment read r of sub-step kk into buffer buf: 0, 1 = B blocks, 2.. = A blocks
+  // one fragment read r of sub-step kk into buffer buf: the B blocks, then the A blocks
   auto read_one = [&](const char* ca, const char* cb, int kk, int buf, int r) {
     const int piece = (((kk * 2 + khalf) ^ swz) << 4);
-    if (r < 2)
+    if (r < NJ)
       bfr[buf][r] = *reinterpret_cast<const bf16x8*>(cb + ta.brow + r * 32 * kBK * 2 + piece);
     else
-      af[buf][r - 2] = *reinterpret_cast<const bf16x8*>(ca + ta.arow + (r - 2) * 32 * kBK * 2 + piece);
+      af[buf][r - NJ] = *reinterpret_cast<const bf16x8*>(ca + ta.arow + (r - NJ) * 32 * kBK * 2 + piece);
   };
   auto mma_one = [&](int buf, int g) {
-    const int i = g >> 1, j = g & 1;
+    const int i = g / NJ, j = g % NJ;
     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[buf][j], af[buf][i], acc[i][j], 0, 0, 0);
   };
   // one direct load n of stage kt + 2 (A, n < 4) or kt + 3 (B, n >= 4, into slot bs)
@@ -192,7 +190,7 @@ __device__ __forceinline__ void mainloop_ni(const TileAddr& ta, int nk, Acc& acc
       const char* a0 = ta.a + (kt + 2) * kBK * 2;
       __builtin_amdgcn_global_load_lds((glob_void*)(a0 + ta.oa[n]), (lds_void*)(st + (8 * n + w) * 1024), 16, 0, 0);
     } else {
-      char* st = lds + kBBase + bs * kOpBytes;
+      char* st = lds + kBBase + bs * kBStage;
       const char* b0 = ta.b + (kt + 3) * kBK * 2;
       __builtin_amdgcn_global_load_lds((glob_void*)(b0 + ta.ob[n - 4]), (lds_void*)(st + (8 * (n - 4) + w) * 1024),
                                        16, 0, 0);
@@ -200,7 +198,8 @@ __device__ __forceinline__ void mainloop_ni(const TileAddr& ta, int nk, Acc& acc
   };
   // kLateB: direct load n of B(kt + 2) into its slot bs2 (that of B(kt - 1))
   auto load_b_late = [&](int kt, int bs2, int n) {
-    char* st = lds + kBBase + bs2 * kOpBytes;
+    static_assert(!kLateB || kBL == 4, "the late loads below are four");
+    char* st = lds + kBBase + bs2 * kBStage;
     const char* b0 = ta.b + (kt + 2) * kBK * 2;
     __builtin_amdgcn_global_load_lds((glob_void*)(b0 + ta.ob[n]), (lds_void*)(st + (8 * n + w) * 1024), 16, 0, 0);
   };
@@ -209,10 +208,10 @@ __device__ __forceinline__ void mainloop_ni(const TileAddr& ta, int nk, Acc& acc
     constexpr bool kIA = decltype(ia_c)::value;
     constexpr bool kIB = decltype(ib_c)::value;
     const char* ca = lds + (kt & 1) * kOpBytes;
-    const char* cb = lds + kBBase + bs * kOpBytes;
+    const char* cb = lds + kBBase + bs * kBStage;
     const int bs_next = bs == 2 ? 0 : bs + 1;
     const char* na = lds + ((kt + 1) & 1) * kOpBytes;
-    const char* nb = lds + kBBase + bs_next * kOpBytes;
+    const char* nb = lds + kBBase + bs_next * kBStage;
     // kLateB: B(kt + 2) exists exactly when A(kt + 2) does
     constexpr bool kLate = kLateB && kIA;
     const int bs_prev = bs == 0 ? 2 : bs - 1;
@@ -241,7 +240,7 @@ __device__ __forceinline__ void mainloop_ni(const TileAddr& ta, int nk, Acc& acc
       // this wave's reads of stage kt are done and its loads of stage kt + 1 have landed (only
       // B(kt + 2) may still be in flight) ... and every wave's (bare s_barrier, see above);
       // kLateB issues B(kt + 2) in this stage, after A(kt + 1), so the count is the same
-      __builtin_amdgcn_s_waitcnt(kIA ? 0x0074 : 0x0070);   // vmcnt(4 or 0) lgkmcnt(0)
+      __builtin_amdgcn_s_waitcnt(kIA ? 0x0070 | kBL : 0x0070);   // vmcnt(kBL or 0) lgkmcnt(0)
       __builtin_amdgcn_s_barrier();
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -249,7 +248,7 @@ __device__ __forceinline__ void mainloop_ni(const TileAddr& ta, int nk, Acc& acc
     // MFMAs, next-stage reads and loads ahead of the SIMD's other wave (measured on the EP FFN:
     // -1.1 %, output unchanged; placing it over sub-steps 0-2 instead was slower).
     __builtin_amdgcn_s_setprio(1);
-    constexpr int kLoads = (kIA ? 4 : 0) + (kIB && !kLateB ? 4 : 0);
+    constexpr int kLoads = (kIA ? 4 : 0) + (kIB && !kLateB ? kBL : 0);
     // sub-step 3: each MFMA followed by one read of the next stage's sub-step 0 and one load
 #pragma unroll
     for (int g = 0; g < kMfma; ++g) {
@@ -288,17 +287,18 @@ __device__ __forceinline__ void mainloop_ni(const TileAddr& ta, int nk, Acc& acc
 // acc = A[0:256, 0:K] * B[rows(0:256), 0:K]^T. Rows of A at or beyond a_rows read row
 // a_rows - 1 and their 32-row blocks are skipped where a whole block is past a_rows (their
 // results are zero or stale and are never stored). Ends with a block barrier, after which the
-// LDS may be reused. Accumulator layout: acc[i][j][q] is output
-//   row wm*128 + 32 i + lane % 32, column wn*64 + 32 j + 8 (q / 4) + 4 (lane / 32) + q % 4.
-template <bool kLateB = false>
+// LDS may be reused. Accumulator layout: acc[i][j][q] of wave (wm, wn) is output row
+// wm*(256 / kWM) + 32 i + lane % 32, column wn*(BN / kWN) + 32 j + 8 (q / 4) + 4 (lane / 32) + q % 4.
+template <bool kLateB = false, int BN = kBN>
 __device__ __forceinline__ void gemm_mainloop(const uint16_t* __restrict__ A, int64_t lda,
                                               int a_rows, const uint16_t* __restrict__ B,
                                               int64_t ldb, int b_n0, int b_half, bool swiglu,
-                                              int K, Acc& acc, char* lds) {
+                                              int K, typename TileShape<BN>::AccT& acc, char* lds) {
+  typedef TileShape<BN> Shape;
   const int lane = threadIdx.x & 63;
   // the wave index is uniform: keep it scalar so the LDS destinations (M0) are scalar math
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wm = w >> 2, wn = w & 3;
+  const int wm = w / Shape::kWN, wn = w % Shape::kWN;
   TileAddr ta;
   ta.a = reinterpret_cast<const char*>(A);
   ta.b = reinterpret_cast<const char*>(B);
@@ -314,43 +314,59 @@ __device__ __forceinline__ void gemm_mainloop(const uint16_t* __restrict__ A, in
     const int r = 64 * i + 8 * w + lr;
     const int ar = r < a_rows ? r : a_rows - 1;
     ta.oa[i] = static_cast<uint32_t>(ar * lda * 2 + c16);
-    ta.ob[i] = static_cast<uint32_t>(b_row_map(r, b_n0, b_half, swiglu) * ldb * 2 + c16);
+    if (i < Shape::kBL) ta.ob[i] = static_cast<uint32_t>(b_row_map(r, b_n0, b_half, swiglu) * ldb * 2 + c16);
   }
-  // fragment reads: row (wm*128 + i*32 + lane%32) of A, (wn*64 + j*32 + lane%32) of B, as
+  // fragment reads: row (wm*kRowsW + i*32 + lane%32) of A, (wn*BN/kWN + j*32 + lane%32) of B, as
   // byte offsets inside a stage buffer
-  ta.arow = (wm * 128 + (lane & 31)) * kBK * 2;
-  ta.brow = (wn * 64 + (lane & 31)) * kBK * 2;
-  zero_acc(acc);
+  constexpr int kRowsW = kBM / Shape::kWM;
+  ta.arow = (wm * kRowsW + (lane & 31)) * kBK * 2;
+  ta.brow = (wn * (BN / Shape::kWN) + (lane & 31)) * kBK * 2;
+#pragma unroll
+  for (int i = 0; i < Shape::kNI; ++i)
+#pragma unroll
+    for (int j = 0; j < Shape::kNJ; ++j)
+#pragma unroll
+      for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
   const int nk = K / kBK;
-  const int valid = a_rows - wm * 128;
-  const int ni = valid >= 128 ? 4 : (valid <= 0 ? 0 : (valid + 31) >> 5);
-  switch (__builtin_amdgcn_readfirstlane(ni)) {
-    case 4: mainloop_ni<4, kLateB>(ta, nk, acc, lds); break;
-    case 3: mainloop_ni<3, kLateB>(ta, nk, acc, lds); break;
-    case 2: mainloop_ni<2, kLateB>(ta, nk, acc, lds); break;
-    case 1: mainloop_ni<1, kLateB>(ta, nk, acc, lds); break;
-    default: mainloop_ni<0, kLateB>(ta, nk, acc, lds); break;
+  const int valid = a_rows - wm * kRowsW;
+  const int ni = __builtin_amdgcn_readfirstlane(valid >= kRowsW ? Shape::kNI : (valid <= 0 ? 0 : (valid + 31) >> 5));
+  if constexpr (Shape::kNI == 4) {
+    switch (ni) {
+      case 4: mainloop_ni<BN, 4, kLateB>(ta, nk, acc, lds); break;
+      case 3: mainloop_ni<BN, 3, kLateB>(ta, nk, acc, lds); break;
+      case 2: mainloop_ni<BN, 2, kLateB>(ta, nk, acc, lds); break;
+      case 1: mainloop_ni<BN, 1, kLateB>(ta, nk, acc, lds); break;
+      default: mainloop_ni<BN, 0, kLateB>(ta, nk, acc, lds); break;
+    }
+  } else {
+    switch (ni) {
+      case 2: mainloop_ni<BN, 2, kLateB>(ta, nk, acc, lds); break;
+      case 1: mainloop_ni<BN, 1, kLateB>(ta, nk, acc, lds); break;
+      default: mainloop_ni<BN, 0, kLateB>(ta, nk, acc, lds); break;
+    }
   }
   __syncthreads();
 }
 
-// Accumulators -> bf16 tile in LDS, row-major [256][kEpiPitch]; four columns per 8-byte write.
-__device__ __forceinline__ void stage_tile(const Acc& acc, char* lds) {
+// Accumulators -> bf16 tile in LDS, row-major [256][kPitch]; four columns per 8-byte write.
+template <int BN = kBN>
+__device__ __forceinline__ void stage_tile(const typename TileShape<BN>::AccT& acc, char* lds) {
+  typedef TileShape<BN> Shape;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int wm = w >> 2, wn = w & 3;
-  const int row0 = wm * 128 + (lane & 31);
-  const int col0 = wn * 64 + 4 * (lane >> 5);
+  const int wm = w / Shape::kWN, wn = w % Shape::kWN;
+  const int row0 = wm * (kBM / Shape::kWM) + (lane & 31);
+  const int col0 = wn * (BN / Shape::kWN) + 4 * (lane >> 5);
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < Shape::kNI; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < Shape::kNJ; ++j)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         uint2 v;
         v.x = pack_bf16x2(acc[i][j][4 * g], acc[i][j][4 * g + 1]);
         v.y = pack_bf16x2(acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
         const int row = row0 + 32 * i, col = col0 + 32 * j + 8 * g;
-        *reinterpret_cast<uint2*>(lds + (row * kEpiPitch + col) * 2) = v;
+        *reinterpret_cast<uint2*>(lds + (row * Shape::kPitch + col) * 2) = v;
       }
 }
 
@@ -383,7 +399,8 @@ __device__ __forceinline__ void stage_swiglu(const Acc& acc, char* lds) {
 }
 
 // Stores staged rows [0, rows) through the per-row destination pointers in LDS (null rows are
-// skipped). cols = 256 (plain) or 128 (SwiGLU). Every piece is one 128-bit store, with kThrough
+// skipped). cols = the tile's columns, or 128 (SwiGLU); threads past the last whole row of a pass sit
+// out. Every piece is one 128-bit store, with kThrough
 // past the L2.
 template <bool kThrough = false>
 __device__ __forceinline__ void store_rows(const char* lds_bytes, int pitch, int cols, int rows,
@@ -394,6 +411,7 @@ __device__ __forceinline__ void store_rows(const char* lds_bytes, int pitch, int
   const int per_row = cols / 8;                // 16-byte pieces per row
   const int rows_per_pass = kThreads / per_row;
   const int pc = tid % per_row;
+  if (tid / per_row >= rows_per_pass) return;
   // global-address stores (a generic pointer would make them flat stores, which also count
   // against the LDS wait counter); no unrolling, so no per-row LDS addresses are held (and
   // spilled) across the loop. (Measured: nontemporal stores here slow the next tiles'

@@ -60,6 +60,44 @@ def test_gemm_split_forms_bitexact(M, N, K, pad):
     assert (got[M:] == 0xFFFF).all() and (got[:, N:] == 0xFFFF).all()
 
 
+# output tiles of 192 and of 128 columns, taken where they fill the CUs better: plain rows with a
+# padded pitch and a ragged last row block, row-block windows, head groups whose heads straddle the
+# tiles and the pieces of a store pass. Integer operands: the bits are unique.
+@pytest.mark.parametrize("M,N", [(4000, 6144), (1999, 4096)])
+def test_gemm_narrow_tiles_bitexact(M, N):
+    X, K = xs(), 320
+    a, b = synth.int_valued_bf16(0, 1, (M, K)), synth.int_valued_bf16(0, 2, (N, K))
+    da, db = dev_bits(a), dev_bits(b)
+    c = torch.full((M + 1, N + 8), -1, dtype=torch.int16, device="cuda")
+    X.check(X.xs_gemm(da.data_ptr(), K, db.data_ptr(), K, c.data_ptr(), N + 8, M, N, K, None, _stream()))
+    got = host_bits(c)
+    assert np.array_equal(got[:M, :N], f64_to_bf16_bits(osc.gemm(a, np.ascontiguousarray(b.T))))
+    assert (got[M:] == 0xFFFF).all() and (got[:, N:] == 0xFFFF).all()
+
+
+@pytest.mark.parametrize("kind,M,N,hd,hpg", [("rows", 4096, 6144, 0, 0), ("rows", 1024, 512, 0, 0),
+                                             ("heads", 1000, 12288, 128, 4), ("heads", 2100, 3840, 40, 4),
+                                             ("heads", 257, 1536, 64, 2), ("heads", 1, 768, 8, 4)])
+def test_scatter_narrow_tiles_bitexact(kind, M, N, hd, hpg):
+    X, K = xs(), 64
+    a, b = synth.int_valued_bf16(0, 1, (M, K)), synth.int_valued_bf16(0, 2, (N, K))
+    ref = f64_to_bf16_bits(osc.gemm(a, np.ascontiguousarray(b.T)))
+    if kind == "rows":
+        W = 4
+        desc, shape = X.xs_scatter_desc(X.XS_SCATTER_ROW_BLOCK, M // W, 0, 0, 0, 0), (W, M // W, N)
+        ref = ref.reshape(shape)
+    else:
+        nh = N // 3 // hd
+        W = nh // hpg
+        desc, shape = X.xs_scatter_desc(X.XS_SCATTER_HEAD_GROUP, 0, 3, nh, hd, hpg), (W, 3 * hpg * M, hd)
+        ref = ref.reshape(M, 3, W, hpg, hd).transpose(2, 1, 3, 0, 4).reshape(shape)
+    da, db = dev_bits(a), dev_bits(b)
+    win = torch.full(shape, -1, dtype=torch.int16, device="cuda")
+    wins = X.windows([X.window(win[d]) for d in range(W)])
+    X.check(X.xs_gemm_scatter(da.data_ptr(), K, db.data_ptr(), K, M, N, K, desc, wins, W, None, None, _stream()))
+    assert np.array_equal(host_bits(win), ref)
+
+
 def test_gemm_integer_operands_bitexact():
     # |sums| < 2^24: fp32 accumulation is exact in any order, so the rounded bits are unique
     a = synth.int_valued_bf16(0, 1, (384, 320))

@@ -379,7 +379,7 @@ __global__ __launch_bounds__(1024) void layout_scan_kernel(int* __restrict__ chu
     }
   }
   window_offsets(run, e, E, epw, cap, start, ws, s_m, expert_offsets, dest_counts, status, pa);
-  if (pa.meta) plan_rows(pa, 256, s_m, s_first, ws);
+  if (pa.meta) plan_rows(pa, s_m, s_first, ws);
 }
 
 // Every slot: final row = expert offset + source base + chunk base + rank in chunk;
@@ -476,7 +476,7 @@ __global__ __launch_bounds__(1024) void layout_small_kernel(const int* __restric
       row_src[static_cast<int64_t>(e[q] / epw) * cap + r] = (s << 24) | (i - s * T * k);
     }
   }
-  if (pa.meta) plan_rows(pa, 256, s_m, s_first, ws);
+  if (pa.meta) plan_rows(pa, s_m, s_first, ws);
 }
 
 // ------------------------------------------------------------------------------ dispatch

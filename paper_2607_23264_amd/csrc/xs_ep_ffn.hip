@@ -58,6 +58,7 @@ struct EpArgs {
   const int* exp_m;
   const int* exp_rowfirst;
   const int* exp_hrow;
+  const int* exp_block;
   const int* wave_pos;
   const int* wave_row;
   int* l1_done;
@@ -92,7 +93,7 @@ __global__ __launch_bounds__(1024) void ep_plan_kernel(const int* __restrict__ e
     }
     s_m[i] = max(0, min(m, pa.cap - off));
   }
-  plan_rows(pa, kBM, s_m, s_first, ws);
+  plan_rows(pa, s_m, s_first, ws);
 }
 
 // Rows [m0, m0 + rows) of local expert x covered by scheduler row p. The expert's m rows fall
@@ -110,7 +111,7 @@ __device__ __forceinline__ void expert_block(const EpArgs& a, int x, int p, bool
                                              int& rows) {
   const int m = a.exp_m[x];
   const int mt = (m + kBM - 1) / kBM;
-  const int bm = equal ? min(kBM, ((m + mt - 1) / mt + 31) & ~31) : kBM;
+  const int bm = equal ? min(kBM, ((m + mt - 1) / mt + 31) & ~31) : (a.exp_block[x] == kSmallRows ? kSmallRows : kBM);
   m0 = (p - a.exp_rowfirst[x]) * bm;
   rows = min(bm, m - m0);
 }
@@ -961,6 +962,7 @@ int fill_args(const xs_ep_layer* L, void* workspace, EpArgs* a, WinSet* dws, Win
   a->exp_m = exp;
   a->exp_rowfirst = exp + L->n_experts;
   a->exp_hrow = exp + 2 * L->n_experts;
+  a->exp_block = exp + 3 * L->n_experts;
   a->row_expert = reinterpret_cast<int*>(ws + w.rowexp_off);
   a->wave_pos = reinterpret_cast<int*>(ws + w.wave_pos_off);
   a->wave_row = reinterpret_cast<int*>(ws + w.wave_row_off);
@@ -971,17 +973,18 @@ int fill_args(const xs_ep_layer* L, void* workspace, EpArgs* a, WinSet* dws, Win
   return XS_OK;
 }
 
-PlanArgs plan_args(const xs_ep_layer* L, const EpArgs& a, int wave_tiles) {
+PlanArgs plan_args(const xs_ep_layer* L, const EpArgs& a, int wave_tiles, int half_tiles) {
   return PlanArgs{L->e_begin, L->n_experts, L->cap, a.P1, a.P2, wave_tiles,
                   const_cast<int*>(a.meta), const_cast<int*>(a.row_expert),
                   const_cast<int*>(a.exp_m), const_cast<int*>(a.exp_rowfirst),
-                  const_cast<int*>(a.exp_hrow), const_cast<int*>(a.wave_pos),
-                  const_cast<int*>(a.wave_row), a.l1_done};
+                  const_cast<int*>(a.exp_hrow), const_cast<int*>(a.exp_block),
+                  const_cast<int*>(a.wave_pos), const_cast<int*>(a.wave_row), a.l1_done, half_tiles,
+                  static_cast<int>(ep_workspace(L).max_rows)};
 }
 
 int launch_plan(const xs_ep_layer* L, const EpArgs& a, int wave_tiles, hipStream_t st) {
   hipLaunchKernelGGL(ep_plan_kernel, dim3(1), dim3(1024), 0, st, L->expert_counts, L->n_src, L->E,
-                     L->expert_offsets, plan_args(L, a, wave_tiles));
+                     L->expert_offsets, plan_args(L, a, wave_tiles, 0));
   return xs_host::launch_status();
 }
 
@@ -1175,7 +1178,15 @@ static int fused_ep_layer(const xs_ep_layer* L, const xs_pacing* pacing, const x
   // standalone calls, and no plan launch).
   const int grid = xs_host::persistent_grid(pacing ? pacing->max_producers : 0);
   const int wave_tiles = pacing && pacing->wave_tiles > 0 ? pacing->wave_tiles : grid;
-  const PlanArgs pa = plan_args(L, a, wave_tiles);
+  // MX tiles of more than 128 rows take twice the time of the small-tile core's: where blocks of 128
+  // rows still are one round of Linear-1 tiles, they shorten the layer (4 sources x 198 tokens of
+  // 2048, 64 experts, MXFP8, skewed: 105 -> 98 us; 1 x 1024 of 512, uniform: 64 -> 55). With a second
+  // round they do not (4 x 512 of 2048, uniform, 384 tiles: 110 -> 128). Paced and traced runs keep
+  // the 256-row order that they name.
+  const bool plain = !pacing || (pacing->policy == XS_POLICY_INTERLEAVE && !pacing->max_producers &&
+                                 !pacing->gap_ns && pacing->withhold_row < 0);
+  const bool halves = is_mx(L) && plain && !(trace && trace->buf && trace->count);
+  const PlanArgs pa = plan_args(L, a, wave_tiles, halves ? grid : 0);
   char* layout_ws = static_cast<char*>(workspace) + w.layout_off;
   rc = xs_host::dispatch_layout(L->topk_idx, L->n_src, L->T, L->k, L->E, L->W, L->cap,
                                 L->expert_counts, L->src_base, L->expert_offsets, L->dest_counts,

@@ -1,5 +1,5 @@
 // The expert FFN's scheduler plan, computed from the local experts' row counts: scheduler rows
-// of up to 256 rows per expert, the Expert-Wave boundaries (App. A.2), the h row offsets, and
+// of up to 256 (or 128) rows per expert, the Expert-Wave boundaries (App. A.2), the h row offsets, and
 // the cleared readiness and claim counters. Shared by the plan kernel and by the layout's
 // scan kernel, which plans right after it has the expert totals.
 #pragma once
@@ -16,9 +16,13 @@ struct PlanArgs {
   int* exp_m;
   int* exp_rowfirst;
   int* exp_hrow;
+  int* exp_block;      // rows of the expert's blocks; not in meta, whose line the claims keep busy
   int* wave_pos;
   int* wave_row;
   int* l1_done;
+  // Blocks of 128 rows where those are at most this many Linear-1 tiles (0: never), and the scheduler
+  // rows that the tables hold
+  int half_tiles, max_rows;
 };
 
 // Inclusive prefix sum over the wave's lanes, by DPP (no LDS round trips): shifts within rows of 16,
@@ -54,16 +58,28 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int* ws, int& total) 
 // (LDS, 16 ints) are this function's scratch. Called by every thread of one block of at least
 // n_experts threads, in whole waves; begins with a block barrier. One thread per expert: one
 // thread for all of them took most of the scan launch (32 experts: 5 us).
-__device__ __forceinline__ void plan_rows(const PlanArgs& pa, int bm, const int* s_m, int* s_first, int* ws) {
+__device__ __forceinline__ void plan_rows(const PlanArgs& pa, const int* s_m, int* s_first, int* ws) {
   const int i = threadIdx.x, n = pa.n_experts;
   lds_sync();
-  const int m = i < n ? s_m[i] : 0, mt = (m + bm - 1) / bm;
-  int rows, hrows;
-  const int first = block_exclusive_scan(mt, ws, rows), hrow = block_exclusive_scan(m, ws, hrows);
+  const int m = i < n ? s_m[i] : 0;
+  int bm = 256, mt = (m + 255) / 256, rows, hrows;
+  int first = block_exclusive_scan(mt, ws, rows);
+  const int hrow = block_exclusive_scan(m, ws, hrows);
+  if (rows > 0 && rows * pa.P1 <= pa.half_tiles) {
+    int rows_half;
+    const int mt_half = (m + 127) / 128, first_half = block_exclusive_scan(mt_half, ws, rows_half);
+    if (rows_half * pa.P1 <= pa.half_tiles && rows_half <= pa.max_rows) {
+      bm = 128;
+      mt = mt_half;
+      first = first_half;
+      rows = rows_half;
+    }
+  }
   if (i < n) {
     pa.exp_m[i] = m;
     pa.exp_rowfirst[i] = first;
     pa.exp_hrow[i] = hrow;
+    pa.exp_block[i] = bm;
     s_first[i] = first + mt;   // the row after the expert's last
     for (int p = first; p < first + mt; ++p) pa.row_expert[p] = i;
   }

@@ -344,6 +344,31 @@ def test_expert_rows_at_block_edges(prec):
         assert_close(host_bits(lay.out), ref["out64"], f"output {prec}")
 
 
+# blocks of 128 rows (few tiles, unpaced) and of 256 (a pacing gap) give the same bits; the last load
+# set is past one round of 128-row tiles on 256 CUs, where both are blocks of 256
+@pytest.mark.parametrize("prec", ["MXFP8", "W4A8"])
+@pytest.mark.parametrize("loads", [[128, 129, 0, 255], [256, 257, 384, 385], [511, 1, 700, 3000]])
+def test_block_rows_give_the_same_bits(prec, loads):
+    from paper_2607_23264_amd.layer import EPLayer, Shape, pacing
+    X = xs()
+    cfg = synth.EPConfig("blocks", T=sum(loads), H=512, E=4, k=1, I=1024, W=4, n_src=1, compute_all=True)
+    inp = synth.ep_inputs(cfg, 3)
+    logits = np.zeros((1, cfg.T, cfg.E), np.float32)
+    logits[0, np.arange(cfg.T), np.random.default_rng(5).permutation(np.repeat(np.arange(cfg.E), loads))] = 4.0
+    lay = EPLayer(Shape(1, cfg.T, cfg.H, cfg.E, 1, cfg.I, cfg.W, 0, cfg.E), precision=getattr(X, f"XS_PREC_{prec}"))
+    lay.upload(logits, inp["x"], inp["w1"], inp["w2"])
+    got = []
+    for p in (None, pacing(X.XS_POLICY_INTERLEAVE, gap_ns=1)):
+        lay.cwin.fill_(-1)
+        lay.out.fill_(-1)
+        lay.fused(p)
+        torch.cuda.synchronize()
+        assert int(lay.status.item()) == 0
+        got.append((host_bits(lay.cwin), host_bits(lay.out)))
+    assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
+    assert not (got[0][1] == 0xFFFF).any()
+
+
 def _records(buf, count):
     n = min(int(count.item()), buf.shape[0])
     r = buf[:n].cpu().numpy().astype(np.uint64)

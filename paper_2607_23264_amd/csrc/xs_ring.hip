@@ -7,8 +7,8 @@
 // order) by a prefix scan before the dispatch; entry n lives in slot n mod S.
 //
 // Lifetime protocol (per slot two words, counting completed uses):
-//   pub[s] = u + 1  entry n = u S + s is written (system-scope release by its producer);
-//   rel[s] = u + 1  it has been copied out (release by its consumer).
+//   pub[s] = u + 1  entry n = u S + s is written (its producer's stores have completed);
+//   rel[s] = u + 1  it has been copied out (by its consumer).
 // The producer of entry n waits for rel[n mod S] == n / S (entry n - S released), writes the
 // row and header, then publishes. Its consumer sees pub == n / S + 1, copies the row into every
 // listed window row, then releases the slot.

@@ -45,10 +45,8 @@ namespace xs {
 
 namespace attn {
 
-typedef __attribute__((address_space(3))) char lds_char;
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
 typedef __bf16 bf16x2_v __attribute__((ext_vector_type(2)));
 
 constexpr int kD = 128;                    // head_dim
@@ -61,25 +59,6 @@ constexpr int kThreads = 256;
 // a query's running maximum is raised (and its sums rescaled) only when a block's maximum
 // exceeds it by more than this many powers of two; until then probabilities stay <= 2^8
 constexpr float kRescaleSlack = 8.f;
-constexpr int kBufDword3 = 0x00020000;     // raw buffer resource: 32-bit data, no swizzle
-
-typedef int v4i __attribute__((ext_vector_type(4)));
-// A raw buffer descriptor over [base, base + bytes): 32-bit data, no stride, no swizzle.
-__device__ __forceinline__ v4i buffer_rsrc(const void* base, int bytes) {
-  const uint64_t b = reinterpret_cast<uint64_t>(base);
-  const v4i r = {static_cast<int>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b))),
-                 static_cast<int>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b >> 32)) & 0xFFFF),
-                 bytes, kBufDword3};
-  return r;
-}
-// One 16-byte piece per lane from the buffer at voff + soff into LDS at dst + 16 lane. Issued
-// from assembly so that the compiler does not count it: it would otherwise wait for every
-// load in flight before each transposing LDS read (it cannot tell the two apart), and the
-// kernel orders these loads itself, with vmcnt waits and workgroup barriers.
-__device__ __forceinline__ void load_lds16(v4i rsrc, uint32_t voff, int soff, const lds_char* dst) {
-  const uint32_t m0v = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(dst));
-  asm volatile("buffer_load_dwordx4 %0, %1, %2 offen lds" :: "v"(voff), "s"(rsrc), "s"(soff), "{m0}"(m0v) : "memory");
-}
 
 __device__ __forceinline__ int k_swz(int r) { return r & 15; }
 __device__ __forceinline__ int v_swz(int r) { return 4 * (r & 3); }

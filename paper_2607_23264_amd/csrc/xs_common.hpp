@@ -57,28 +57,39 @@ typedef __attribute__((address_space(3))) char lds_char;
 typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
 typedef int v4i __attribute__((ext_vector_type(4)));
 
-// A raw buffer descriptor over [base, base + bytes): loads past its end fetch nothing.
+// A raw buffer descriptor over [base, base + bytes), wave-uniform: loads past its end fetch nothing.
+// A memory instruction may read an SGPR that a vector instruction (readfirstlane) wrote only five
+// wait states later, which the compiler does not see to for the assembly below: hence the s_nop.
 __device__ __forceinline__ v4i buffer_rsrc(const void* base, uint32_t bytes) {
   const uint64_t b = reinterpret_cast<uint64_t>(base);
-  const v4i r = {static_cast<int>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b))),
-                 static_cast<int>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b >> 32)) & 0xFFFF),
-                 static_cast<int>(__builtin_amdgcn_readfirstlane(bytes)), 0x00020000};
+  v4i r = {static_cast<int>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b))),
+           static_cast<int>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b >> 32)) & 0xFFFF),
+           static_cast<int>(bytes), 0x00020000};
+  asm("s_nop 4" : "+s"(r));
   return r;
 }
 
-// One 16-byte piece per lane from the buffer at voff into LDS at dst + 16 lane. Issued from
-// assembly so that the compiler does not count it (it would wait for every load in flight
-// before each LDS read); the kernel waits itself, with vmcnt.
+// One 16-byte piece per lane from the buffer at voff (+ soff) into LDS at dst + 16 lane. Issued from
+// assembly so that the compiler does not count it: it would wait for every load in flight
+// before each LDS read (for transposing reads it cannot tell the two apart); the kernel waits itself,
+// with vmcnt. A load into LDS may not directly follow the write of M0 that gives its address
+// (one wait state), which the compiler does not see to around assembly: hence the s_nop.
 __device__ __forceinline__ void load_lds16(v4i rsrc, uint32_t voff, const lds_char* dst) {
   const uint32_t m0v = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(dst));
-  asm volatile("buffer_load_dwordx4 %0, %1, 0 offen lds" :: "v"(voff), "s"(rsrc), "{m0}"(m0v) : "memory");
+  asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" :: "v"(voff), "s"(rsrc), "{m0}"(m0v) : "memory");
+}
+__device__ __forceinline__ void load_lds16(v4i rsrc, uint32_t voff, int soff, const lds_char* dst) {
+  const uint32_t m0v = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(dst));
+  asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+               :: "v"(voff), "s"(rsrc), "s"(soff), "{m0}"(m0v) : "memory");
 }
 
 // A store past the L2 (agent scope, written through to memory): once it has completed (vmcnt), an
 // agent-scope acquire on any XCD sees it, without the release that writes back the whole L2. Not
-// counted by the compiler: the kernel waits with wait_vm.
+// counted by the compiler: the kernel waits with wait_vm. (The registers of a store of more than 64
+// bits may be written again two wait states later; the compiler does not see to that here.)
 __device__ __forceinline__ void store_through16(void* p, u32x4 v) {
-  asm volatile("global_store_dwordx4 %0, %1, off sc1" :: "v"(p), "v"(v) : "memory");
+  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" :: "v"(p), "v"(v) : "memory");
 }
 __device__ __forceinline__ void store_through4(void* p, uint32_t v) {
   asm volatile("global_store_dword %0, %1, off sc1" :: "v"(p), "v"(v) : "memory");

@@ -57,7 +57,8 @@ struct RingArgs {
   const int* slot_row;         // [T][k] window row of each (token, k) slot
   WinSet win;                  // dispatch windows
   char* ring[XS_MAX_WINDOWS];  // ring memory per destination: S slots of slot_bytes
-  int64_t slot_bytes;          // payload, then 1 + k header ints
+  int64_t slot_bytes;          // from one slot to the next (no upper bound)
+  uint32_t entry_bytes;        // payload, then 1 + k header ints
   int* entry_no;               // [T][k] entry number of each (token, k) slot in its ring, less its
                                //        chunk's base
   int* chunk_base;             // [T / kChunk][W] entries of the ring from earlier chunks
@@ -163,12 +164,13 @@ __device__ __forceinline__ int bcast(int v) { return __builtin_amdgcn_readfirstl
 
 typedef __attribute__((address_space(1))) u32x4 gv4;
 
-// A buffer over one ring slot (wave-uniform address).
+// A buffer over the entry in one ring slot (wave-uniform address). Its range is the entry's bytes and not
+// the slots' distance, which may not fit a descriptor's 32 bits.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t slot_buffer(const RingArgs& a, int d, int s) {
   const uint64_t p = reinterpret_cast<uint64_t>(a.ring[d] + static_cast<int64_t>(s) * a.slot_bytes);
   const uint64_t u = static_cast<uint64_t>(static_cast<uint32_t>(bcast(static_cast<int>(p)))) |
                      static_cast<uint64_t>(static_cast<uint32_t>(bcast(static_cast<int>(p >> 32)))) << 32;
-  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(u), 0, static_cast<int>(a.slot_bytes), 0x00020000);
+  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(u), 0, static_cast<int>(a.entry_bytes), 0x00020000);
 }
 
 // Copies published entry m of ring d out and releases its slot (wave-uniform m, d).
@@ -433,6 +435,7 @@ extern "C" int xs_dispatch_ring(const void* x, int32_t T, int32_t H, const int32
   a.idx = topk_idx;
   a.slot_row = slot_row;
   a.slot_bytes = rings[0].row_stride_bytes;
+  a.entry_bytes = static_cast<uint32_t>(static_cast<int64_t>(H) * 2 + 4 * (1 + k));
   a.total = ctrl + kCtrlTotal;
   a.abort_word = ctrl + kCtrlAbort;
   a.pub = ctrl + kCtrlPub;

@@ -30,13 +30,16 @@ def _stream():
 class Rings:
     """W rings of S slots in device memory, or in host-coherent memory."""
 
-    def __init__(self, T, W, S, H, k, host=False):
+    def __init__(self, T, W, S, H, k, host=False, stride=None):
         X = xs()
         nb = C.c_int64()
         X.check(X.xs_ring_slot_bytes(H, k, C.byref(nb)))
         self.slot_bytes = nb.value
         self.host = None
-        if host:
+        if stride:
+            self.mem = [torch.empty((S - 1) * stride + self.slot_bytes, dtype=torch.uint8, device="cuda") for _ in range(W)]
+            self.arr = X.windows([X.window((m.data_ptr(), S, stride)) for m in self.mem])
+        elif host:
             from paper_2607_23264_amd.layer import HostCoherent
             self.host = HostCoherent(W * S * self.slot_bytes)
             base = self.host.ptr
@@ -62,13 +65,14 @@ def _setup(T, H, E, k, W, seed, cap=None):
     return idx, lay["slot_row"][0], cap, x
 
 
-def _ring_dispatch(x, idx, sr, E, W, cap, S, dedup, host=False, max_producers=0, timeout_us=0):
+def _ring_dispatch(x, idx, sr, E, W, cap, S, dedup, host=False, max_producers=0, timeout_us=0,
+                   stride=None):
     X = xs()
     T, H = x.shape
     k = idx.shape[1]
     win = torch.full((W, cap, H), -1, dtype=torch.int16, device="cuda")
     wins = X.windows([X.window(win[d]) for d in range(W)])
-    rings = Rings(T, W, S, H, k, host)
+    rings = Rings(T, W, S, H, k, host, stride)
     st = torch.zeros((1,), dtype=torch.int32, device="cuda")
     stats = torch.full((2 * W,), -1, dtype=torch.int32, device="cuda")
     dx, di, ds = dev_bits(x), torch.from_numpy(idx).cuda(), torch.from_numpy(np.ascontiguousarray(sr)).cuda()
@@ -102,6 +106,19 @@ def test_ring_windows_equal_plain_dispatch(S, dedup):
 def test_ring_agent_layouts(T, H, E, k, W, S, dedup):
     idx, sr, cap, x = _setup(T, H, E, k, W, T + k)
     got, st, stats = _ring_dispatch(x, idx, sr, E, W, cap, S, dedup)
+    assert st == 0
+    want, _ = oep.dispatch(x[None], idx[None], sr[None], E, W, cap)
+    assert np.array_equal(got, want)
+    assert stats[:W].tolist() == [len(e) for e in oring.ring_entries(idx, sr, E, W, bool(dedup))]
+
+
+# slots further apart than their entries, by a little and by more than 32 bits hold
+@pytest.mark.parametrize("S,stride", [(3, 1024), (3, 1 << 31), (1, 1 << 32), (2, 1 << 32), (2, (1 << 32) + 64)])
+@pytest.mark.parametrize("dedup", [0, 1])
+def test_ring_slots_far_apart(S, stride, dedup):
+    T, H, E, k, W = 70, 264, 16, 4, 2
+    idx, sr, cap, x = _setup(T, H, E, k, W, S)
+    got, st, stats = _ring_dispatch(x, idx, sr, E, W, cap, S, dedup, stride=stride)
     assert st == 0
     want, _ = oep.dispatch(x[None], idx[None], sr[None], E, W, cap)
     assert np.array_equal(got, want)

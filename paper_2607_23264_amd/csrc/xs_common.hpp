@@ -95,6 +95,13 @@ __device__ __forceinline__ void store_through4(void* p, uint32_t v) {
   asm volatile("global_store_dword %0, %1, off sc1" :: "v"(p), "v"(v) : "memory");
 }
 
+// A uniform value, taken where it stands: what follows from it is computed there and not hoisted
+// out of a persistent kernel's tile loop, where it would hold (and spill) registers across tiles.
+__device__ __forceinline__ int uniform_here(int v) {
+  asm volatile("" : "+s"(v));
+  return v;
+}
+
 // Workgroup barrier for data exchanged in LDS only: global stores may still be in flight
 // (__syncthreads waits until they have reached memory, a microsecond or two each time).
 __device__ __forceinline__ void lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }

@@ -217,7 +217,6 @@ __device__ __forceinline__ void count_l1_tile(const EpArgs& a, int p) {
 
 __device__ __forceinline__ void ep_l1_tile(const EpArgs& a, int p, int nt, bool fused,
                                            char* lds, char** rowptr, Claim* cl) {
-  const int tid = threadIdx.x;
   const int x = a.row_expert[p];
   const int e = a.e_begin + x;
   const int dl = e / a.epw - a.d_first;
@@ -232,6 +231,7 @@ __device__ __forceinline__ void ep_l1_tile(const EpArgs& a, int p, int nt, bool 
   const auto put_rows = [&] {
     claim_load(a, cl);
     const uint64_t t = a.tr.buf ? wall_ticks() : 0;
+    const int tid = tid_here();   // nothing derived from it is held across the mainloop
     if (tid < rows)
       rowptr[tid] = reinterpret_cast<char*>(
           a.h + static_cast<int64_t>(a.exp_hrow[x] + m0 + tid) * a.I + nt * (kBN / 2));
@@ -258,7 +258,7 @@ __device__ __forceinline__ void ep_l1_tile(const EpArgs& a, int p, int nt, bool 
     store_rows(lds, kEpiPitchH, kBN / 2, rows, rowptr);
     lds_barrier();   // the unfused h rows are read by a later launch
   }
-  if (a.tr.buf && tid == 0)
+  if (a.tr.buf && threadIdx.x == 0)
     trace_tile(a, 1, static_cast<uint32_t>(p * a.P1 + nt), t0, t1, wall_ticks(), t0, stw,
                static_cast<uint64_t>(rows) * (kBN / 2) * 2, rows);
 }
@@ -292,7 +292,6 @@ __device__ __forceinline__ bool ep_wait_row(const EpArgs& a, int p, int* flag) {
 
 __device__ __forceinline__ void ep_l2_tile(const EpArgs& a, int p, int nt, bool fused,
                                            char* lds, char** rowptr, int* flag, Claim* cl) {
-  const int tid = threadIdx.x;
   const uint64_t t0 = a.tr.buf ? wall_ticks() : 0;
   if (fused && !ep_wait_row(a, p, flag)) return;
   const uint64_t t_dep = a.tr.buf ? wall_ticks() : 0;
@@ -307,11 +306,12 @@ __device__ __forceinline__ void ep_l2_tile(const EpArgs& a, int p, int nt, bool 
   // the destination of this thread's output row, loaded before the mainloop so that its
   // latency is hidden behind the MFMAs
   int code = -1;
-  if (a.l2_combine && tid < rows)
-    code = a.row_src[static_cast<int64_t>(e / a.epw) * a.cap + a.expert_offsets[e] + m0 + tid];
+  if (a.l2_combine && static_cast<int>(threadIdx.x) < rows)
+    code = a.row_src[static_cast<int64_t>(e / a.epw) * a.cap + a.expert_offsets[e] + m0 + threadIdx.x];
   const auto put_rows = [&] {
     claim_load(a, cl);
     const uint64_t t = a.tr.buf ? wall_ticks() : 0;
+    const int tid = tid_here();
     if (tid >= rows) return t;
     char* ptr;
     if (a.l2_combine) {
@@ -347,7 +347,7 @@ __device__ __forceinline__ void ep_l2_tile(const EpArgs& a, int p, int nt, bool 
   // The combine rows are read only after the kernel (window signal, combine-reduce): the
   // stores drain while the next tile runs.
   lds_barrier();
-  if (tid == 0) {
+  if (threadIdx.x == 0) {
     if (a.tr.buf)
       trace_tile(a, 2, static_cast<uint32_t>(p * a.P2 + nt), t0, t1, wall_ticks(), t_dep, stw,
                  static_cast<uint64_t>(rows) * kBN * 2, rows);
@@ -578,51 +578,23 @@ __device__ __forceinline__ int claim_next(const EpArgs& a, Claim& cl) {
   return ep_claim(a, cl);
 }
 
-template <int MODE, int PREC>
-__device__ __forceinline__ void ep_dynamic(const EpArgs& a, int n1, int n2, char* lds, char** rowptr,
-                                           int* flag) {
-  constexpr bool fused = MODE == 3;
-  Claim cl{fused ? 1 : 0, n1, n2, 0, n2 > 0 ? -1 : -2, 0, 0, 0, 0};   // thread 0 only
-  if (fused && a.policy == XS_POLICY_BURST) {
-    const int nw = a.meta[1], total = a.meta[2];
-    for (;;) {
-      if (threadIdx.x == 0)
-        flag[1] = __hip_atomic_fetch_add(a.claim_ctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __syncthreads();
-      const int pos = flag[1];
-      __syncthreads();
-      if (pos >= total) return;
-      int w = 0;
-      while (w + 1 < nw && a.wave_pos[w + 1] <= pos) ++w;
-      const int off = pos - a.wave_pos[w];
-      const int r0 = a.wave_row[w], nl1 = (a.wave_row[w + 1] - r0) * a.P1;
-      if (off < nl1) {
-        const int k1 = r0 * a.P1 + off;
-        l1_tile<PREC>(a, k1 / a.P1, k1 % a.P1, true, lds, rowptr);
-      } else {
-        const int k2 = r0 * a.P2 + (off - nl1);
-        l2_tile<PREC>(a, k2 / a.P2, k2 % a.P2, true, lds, rowptr, flag);
-      }
-    }
-  }
-  for (;;) {
-    if (threadIdx.x == 0) flag[1] = claim_next(a, cl);
-    __syncthreads();
-    const int t = flag[1];
-    __syncthreads();
-    if (t == -1) return;
-    if (t > 0) {
-      const int k1 = t - 1;
-      l1_tile<PREC>(a, k1 / a.P1, k1 % a.P1, fused, lds, rowptr, &cl);
-    } else {
-      const int k2 = -t - 2;
-      l2_tile<PREC>(a, k2 / a.P2, k2 % a.P2, fused, lds, rowptr, flag, &cl);
-    }
-  }
+// Position `pos` of the Expert-Wave list as an entry (as ep_claim); w: the wave of the instance's last
+// position (positions only grow). -1 past the list's end.
+__device__ __forceinline__ int wave_entry(const EpArgs& a, int pos, int& w) {
+  if (pos >= a.meta[2]) return -1;
+  const int nw = a.meta[1];
+  while (w + 1 < nw && a.wave_pos[w + 1] <= pos) ++w;
+  const int off = pos - a.wave_pos[w];
+  const int r0 = a.wave_row[w], nl1 = (a.wave_row[w + 1] - r0) * a.P1;
+  return off < nl1 ? r0 * a.P1 + off + 1 : -(r0 * a.P2 + (off - nl1)) - 2;
 }
 
 // MODE 3: fused Linear-1 + Linear-2 (the EP layer); 1 / 2: one GEMM stream only (unfused
-// expert FFN). A template parameter so each variant is its own kernel in a trace.
+// expert FFN). A template parameter so each variant is its own kernel in a trace. One loop for
+// every policy and claim mode, so that each tile body, with all its mainloops, is in the kernel
+// once: with a loop per policy and claim mode (four copies) the MXFP8 kernel spilled 73 vector
+// registers and the W4A8 one 77, where it is 20 and 24 now, in 40 % of the code (one share, 509
+// tokens of 8 sources, skewed, MXFP8: 443.5 -> 430.6 us; bf16 and W4A8 decode unchanged).
 template <int MODE, int PREC>
 __device__ __forceinline__ void ep_ffn_body(const EpArgs& a, char* smem) {
   char* lds = smem;
@@ -634,44 +606,46 @@ __device__ __forceinline__ void ep_ffn_body(const EpArgs& a, char* smem) {
   constexpr bool fused = MODE == 3;
   const int n1 = (MODE & 1) ? P * a.P1 : 0;
   const int n2 = (MODE & 2) ? P * a.P2 : 0;
-  if (fused && a.policy == XS_POLICY_BURST) {
-    const int nw = a.meta[1], total = a.meta[2];
-    int w = 0;
-    for (int pos = g; pos < total; pos += G) {
-      while (w + 1 < nw && a.wave_pos[w + 1] <= pos) ++w;
-      const int off = pos - a.wave_pos[w];
-      const int r0 = a.wave_row[w], nl1 = (a.wave_row[w + 1] - r0) * a.P1;
-      if (off < nl1) {
-        const int k1 = r0 * a.P1 + off;
-        l1_tile<PREC>(a, k1 / a.P1, k1 % a.P1, true, lds, rowptr);
-      } else {
-        const int k2 = r0 * a.P2 + (off - nl1);
-        l2_tile<PREC>(a, k2 / a.P2, k2 % a.P2, true, lds, rowptr, flag);
-      }
-    }
-    return;
-  }
-  if (a.claim == XS_CLAIM_DYNAMIC) {
-    ep_dynamic<MODE, PREC>(a, n1, n2, lds, rowptr, flag);
-    return;
-  }
-  // Static claiming: this instance owns entries g, g + G, ... of each stream and applies the
-  // claim rule to its own next entries (its own Linear-1 entries play the part of the shared
-  // frontier). An owned Linear-2 entry then only waits on rows whose Linear-1 tiles every
-  // instance has already passed, so with D >= 1 the lowest waited-on row always has running
-  // owners.
-  int e1 = g, e2 = g, run = 0;
+  const bool burst = fused && a.policy == XS_POLICY_BURST, dynamic = a.claim == XS_CLAIM_DYNAMIC;
+  Claim cl{fused && dynamic && !burst ? 1 : 0, n1, n2, 0, n2 > 0 ? -1 : -2, 0, 0, 0, 0};   // thread 0 only
+  // Static claiming: this instance owns entries g, g + G, ... of each stream (or of the
+  // Expert-Wave list) and applies the claim rule to its own next entries (its own Linear-1
+  // entries play the part of the shared frontier). An owned Linear-2 entry then only waits on
+  // rows whose Linear-1 tiles every instance has already passed, so with D >= 1 the lowest
+  // waited-on row always has running owners.
+  int e1 = g, e2 = g, run = 0, w = 0;
   for (;;) {
-    if (e2 < n2 && l2_may_run(a, e2, e1, n1, run)) {
-      l2_tile<PREC>(a, e2 / a.P2, e2 % a.P2, fused, lds, rowptr, flag);
+    int t;
+    if (dynamic) {
+      if (threadIdx.x == 0)
+        flag[1] = burst ? __hip_atomic_fetch_add(a.claim_ctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                        : claim_next(a, cl);
+      __syncthreads();
+      t = __builtin_amdgcn_readfirstlane(flag[1]);
+      __syncthreads();
+    } else if (burst) {
+      t = e1;
+      e1 += G;
+    } else if (e2 < n2 && l2_may_run(a, e2, e1, n1, run)) {
+      t = -e2 - 2;
       e2 += G;
       ++run;
     } else if (e1 < n1) {
-      l1_tile<PREC>(a, e1 / a.P1, e1 % a.P1, fused, lds, rowptr);
+      t = e1 + 1;
       e1 += G;
       run = 0;
     } else {
-      break;
+      t = -1;
+    }
+    if (burst) t = wave_entry(a, t, w);
+    if (t == -1) return;
+    cl.c1 = cl.c2 = cl.kind = cl.k = 0;   // set again after the mainloop: no registers held across it
+    if (t > 0) {
+      const int k1 = t - 1;
+      l1_tile<PREC>(a, k1 / a.P1, k1 % a.P1, fused, lds, rowptr, &cl);
+    } else {
+      const int k2 = -t - 2;
+      l2_tile<PREC>(a, k2 / a.P2, k2 % a.P2, fused, lds, rowptr, flag, &cl);
     }
   }
 }

@@ -356,7 +356,7 @@ __device__ __forceinline__ void gemm_mainloop_mx(const uint8_t* __restrict__ A, 
     for (int j = 0; j < 4; ++j)
 #pragma unroll
       for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
-  const int nk = K / 128;
+  const int nk = uniform_here(K / 128);
   const int valid = a_rows - wm * 128;
   const int ni = valid >= 128 ? 4 : (valid <= 0 ? 0 : (valid + 31) >> 5);
   switch (__builtin_amdgcn_readfirstlane(ni)) {

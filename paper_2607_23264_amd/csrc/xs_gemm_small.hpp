@@ -107,7 +107,7 @@ __device__ __forceinline__ int gemm_mainloop_small(const uint16_t* A, int64_t ld
   for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int q = 0; q < 16; ++q) acc[i][q] = 0.f;
-  const int nk = K / kBK, ni = __builtin_amdgcn_readfirstlane((a_rows + 31) >> 5);
+  const int nk = uniform_here(K / kBK), ni = __builtin_amdgcn_readfirstlane((a_rows + 31) >> 5);
   switch (ni) {
     case 1: mainloop_small<1>(t, nk, acc, lds); break;
     case 2: mainloop_small<2>(t, nk, acc, lds); break;
@@ -330,7 +330,7 @@ __device__ __forceinline__ int gemm_mainloop_mx_small(const uint8_t* A, int64_t 
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
-  const int nk = K / (BF4 ? 256 : 128), ni = __builtin_amdgcn_readfirstlane((a_rows + 31) >> 5);
+  const int nk = uniform_here(K / (BF4 ? 256 : 128)), ni = __builtin_amdgcn_readfirstlane((a_rows + 31) >> 5);
   switch (ni) {
     case 1: mainloop_mx_small<1, BF4>(t, nk, acc, lds); break;
     case 2: mainloop_mx_small<2, BF4>(t, nk, acc, lds); break;

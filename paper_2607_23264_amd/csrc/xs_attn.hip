@@ -311,12 +311,23 @@ __global__ __launch_bounds__(kThreads, 3) void attn_kernel(Args a) {
 // apart in lock step (K product, softmax, V product) were slower than this: 85 us at 4096.
 constexpr int kPartialBytes = 16 * 1024 + 512;   // one wave's unnormalised O' and (max, sum), in lane order
 
+// Two loads as load_lds16 from one write of M0: an instruction's offset counts in the buffer and in
+// LDS, so the second takes voff1 + STEP + soff to dst + STEP + 16 lane. A write of M0 costs itself and
+// its wait state; the lone waves of <1, 4, 32> issue 16 loads a step (1 head x 7296 tokens: 65.7 us
+// with one load per write, 62.4 with two, 63.3 to 63.8 with four).
+template <int STEP>
+__device__ __forceinline__ void load_lds16_pair(v4i rsrc, uint32_t voff0, uint32_t voff1, int soff, const lds_char* dst) {
+  static_assert(STEP < 4096, "twelve bits of instruction offset");
+  const uint32_t m0v = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(dst));
+  asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %0, %2, %3 offen lds\n\tbuffer_load_dwordx4 %1, %2, %3 offen offset:%4 lds"
+               :: "v"(voff0), "v"(voff1), "s"(rsrc), "s"(soff), "n"(STEP), "{m0}"(m0v) : "memory");
+}
+
 template <int QW, int KS, int BKV>
 __global__ __launch_bounds__(QW * KS * 64) void attn_split_kernel(Args a) {
   constexpr int kQ = 32 * QW;                    // queries per output tile
   constexpr int kTile = BKV * kRowBytes;         // bytes of a K or V tile
   constexpr int kNB = BKV / 32;                  // 32-key blocks of a tile
-  constexpr int kLd = kTile / 1024 / QW;         // direct loads per tile and wave
   constexpr int kStage = KS * 4 * kTile, kJoin = KS * QW * kPartialBytes;
   __shared__ __attribute__((aligned(16))) char lds_raw[kStage > kJoin ? kStage : kJoin];
   lds_char* const lds = (lds_char*)lds_raw;
@@ -329,13 +340,15 @@ __global__ __launch_bounds__(QW * KS * 64) void attn_split_kernel(Args a) {
   static_assert(128 % (KS * BKV) == 0, "M is a multiple of 128: every group has the same number of tiles");
   const int n = a.M / (KS * BKV);                // K/V tiles of each group
   const int base = grp * 4 * kTile;              // this group's slots: K 0, K 1, V 0, V 1
-  // lane offsets as in the kernel above
-  uint32_t ko[kLd], vo[kLd];
+  // lane offsets as in the kernel above. A wave's load i takes rows 4 (QW i + w) .. + 3, 1024 (QW i + w)
+  // bytes into the tile and into its slot; the swizzles (of rows mod 16) repeat every 4 KiB.
+  constexpr int kRep = 4 / QW, kStep = QW * 1024;
+  uint32_t ko[kRep], vo[kRep];
 #pragma unroll
-  for (int i = 0; i < kLd; ++i) {
-    const int r = 4 * (QW * i + w) + (lane >> 4);
-    ko[i] = static_cast<uint32_t>(r * kRowBytes + (((lane & 15) ^ k_swz(r)) << 4));
-    vo[i] = static_cast<uint32_t>(r * kRowBytes + (((lane & 15) ^ v_swz(r)) << 4));
+  for (int i = 0; i < kRep; ++i) {
+    const int r = 4 * w + (lane >> 4), rs = r + 4 * QW * i;
+    ko[i] = static_cast<uint32_t>(r * kRowBytes + (((lane & 15) ^ k_swz(rs)) << 4));
+    vo[i] = static_cast<uint32_t>(r * kRowBytes + (((lane & 15) ^ v_swz(rs)) << 4));
   }
   const int krow = lane & 31;
   uint32_t kofs[8];
@@ -359,12 +372,22 @@ __global__ __launch_bounds__(QW * KS * 64) void attn_split_kernel(Args a) {
     const v4i krs = buffer_rsrc(a.k + hoff, a.M * kRowBytes);
     const v4i vrs = buffer_rsrc(a.v + hoff, a.M * kRowBytes);
     auto issue = [&](int j) {                    // the group's K/V tile j into slots j % 2
-      lds_char* st = lds + base + (j & 1) * kTile;
+      lds_char* st = lds + base + (j & 1) * kTile + w * 1024;
       const int so = (grp + KS * j) * kTile;
+      auto tile = [&](v4i rs, const uint32_t (&off)[kRep], lds_char* slot) {
 #pragma unroll
-      for (int i = 0; i < kLd; ++i) load_lds16(krs, ko[i], so, st + (QW * i + w) * 1024);
+        for (int b = 0; b < kTile; b += 4096) {
+          if constexpr (kRep == 1) {
+            load_lds16(rs, off[0], so + b, slot + b);
+          } else {
 #pragma unroll
-      for (int i = 0; i < kLd; ++i) load_lds16(vrs, vo[i], so, st + 2 * kTile + (QW * i + w) * 1024);
+            for (int i = 0; i < kRep; i += 2)
+              load_lds16_pair<kStep>(rs, off[i] + i * kStep, off[i + 1] + i * kStep, so + b, slot + b + i * kStep);
+          }
+        }
+      };
+      tile(krs, ko, st);
+      tile(vrs, vo, st + 2 * kTile);
     };
     issue(0);
     bf16x8 qf[8];

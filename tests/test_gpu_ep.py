@@ -115,7 +115,7 @@ def _idx_random(n_src, T, k, E, seed):
                                            (2, 1, 1, 4, 2), (1, 257, 8, 1024, 64), (64, 16, 4, 160, 32),
                                            (65, 15, 4, 160, 32), (1, 128, 32, 1024, 2), (1, 129, 32, 1024, 2),
                                            (10, 50, 8, 1024, 64), (1, 4096, 1, 16, 16), (1, 4097, 1, 16, 16),
-                                           (3, 20, 33, 64, 4)])
+                                           (3, 20, 33, 64, 4), (2, 300, 33, 64, 4), (1, 4097, 40, 48, 3)])
 def test_layout_matches_oracle(n_src, T, k, E, W):
     idx = _idx_random(n_src, T, k, E, seed=T + E)
     cap = n_src * T * k
@@ -153,6 +153,23 @@ def test_layout_capacity_and_bad_expert_status():
     dup[0, 7, 1] = dup[0, 7, 0]         # one token lists an expert twice
     assert oep.dispatch_layout(dup, 4, 2, cap=128)["status"] == xs().XS_EBADINPUT
     assert _layout_gpu(dup, 4, 2, cap=128)["status"] == xs().XS_EBADINPUT
+
+
+# the same beyond the one-workgroup layout, with the slots in registers (up to 8, up to 32) and not
+@pytest.mark.parametrize("n_src,T,k,E", [(1, 3000, 2, 4), (2, 300, 12, 64), (2, 300, 33, 64)])
+def test_large_layout_capacity_and_bad_expert_status(n_src, T, k, E):
+    idx = _idx_random(n_src, T, k, E, seed=3)
+    full = n_src * T * k
+    got = _layout_gpu(idx, E, 2, cap=10)
+    assert got["status"] == xs().XS_ECAPACITY
+    assert np.array_equal(got["slot_row"], oep.dispatch_layout(idx, E, 2, cap=10)["slot_row"])
+    for expert in (E, -1):
+        bad = idx.copy()
+        bad[-1, T - 1, k - 1] = expert
+        assert _layout_gpu(bad, E, 2, cap=full)["status"] == xs().XS_EBADINPUT
+    dup = idx.copy()
+    dup[-1, 7, k - 1] = dup[-1, 7, 0]
+    assert _layout_gpu(dup, E, 2, cap=full)["status"] == xs().XS_EBADINPUT
 
 
 def _ep_layer(cfg, seed=0, **kw):

@@ -360,15 +360,14 @@ __device__ __forceinline__ int xcd_instance_ep(int b, int G) {
   return (G % 8) ? b : (b % 8) * (G / 8) + b / 8;
 }
 
-// MX tiles (256 threads, the MX core); BF4: the weights are packed E2M1 (W4A8), else E4M3.
+// MX tiles of the fused layer (256 threads, the MX core); BF4: the weights are packed E2M1 (W4A8), else E4M3.
 // Weight scales are grouped by 512 K elements ([K / 512][n_experts * rows][16 bytes]), so a
 // quarter of a scale group is one contiguous run of rows. Linear-1: the dispatch window rows
 // hold H codes then H / 32 scales; the SwiGLU output is quantized in the epilogue into h code
 // rows of I bytes (this tile's 128 columns at 128 nt) and one scale word per row into the h
 // scale groups (group nt / 4, word nt % 4).
 template <bool BF4>
-__device__ __forceinline__ void ep_l1_tile_mx(const EpArgs& a, int p, int nt, bool fused, char* lds,
-                                              char** rowptr, Claim* cl) {
+__device__ __forceinline__ void ep_l1_tile_mx(const EpArgs& a, int p, int nt, char* lds, char** rowptr, Claim* cl) {
   const int x = a.row_expert[p];
   const int e = a.e_begin + x;
   const int dl = e / a.epw - a.d_first;
@@ -439,10 +438,10 @@ __device__ __forceinline__ void ep_l1_tile_mx(const EpArgs& a, int p, int nt, bo
 
 // Linear-2 on MXFP8 h rows; bf16 output rows into the combine windows as in the bf16 tile.
 template <bool BF4>
-__device__ __forceinline__ void ep_l2_tile_mx(const EpArgs& a, int p, int nt, bool fused, char* lds,
-                                              char** rowptr, int* flag, Claim* cl) {
+__device__ __forceinline__ void ep_l2_tile_mx(const EpArgs& a, int p, int nt, char* lds, char** rowptr, int* flag,
+                                              Claim* cl) {
   const uint64_t t0 = a.tr.buf ? wall_ticks() : 0;
-  if (fused && !ep_wait_row(a, p, flag)) return;
+  if (!ep_wait_row(a, p, flag)) return;
   const uint64_t t_dep = a.tr.buf ? wall_ticks() : 0;
   const uint64_t stw = staging_wait(a);
   const int x = a.row_expert[p];
@@ -506,13 +505,13 @@ __device__ __forceinline__ void ep_l2_tile_mx(const EpArgs& a, int p, int nt, bo
 template <int PREC>
 __device__ __forceinline__ void l1_tile(const EpArgs& a, int p, int nt, bool fused, char* lds, char** rowptr,
                                         Claim* cl = nullptr) {
-  if constexpr (PREC > 0) ep_l1_tile_mx<PREC == 2>(a, p, nt, fused, lds, rowptr, cl);
+  if constexpr (PREC > 0) ep_l1_tile_mx<PREC == 2>(a, p, nt, lds, rowptr, cl);
   else ep_l1_tile(a, p, nt, fused, lds, rowptr, cl);
 }
 template <int PREC>
 __device__ __forceinline__ void l2_tile(const EpArgs& a, int p, int nt, bool fused, char* lds, char** rowptr,
                                         int* flag, Claim* cl = nullptr) {
-  if constexpr (PREC > 0) ep_l2_tile_mx<PREC == 2>(a, p, nt, fused, lds, rowptr, flag, cl);
+  if constexpr (PREC > 0) ep_l2_tile_mx<PREC == 2>(a, p, nt, lds, rowptr, flag, cl);
   else ep_l2_tile(a, p, nt, fused, lds, rowptr, flag, cl);
 }
 
@@ -604,6 +603,7 @@ __device__ __forceinline__ void ep_ffn_body(const EpArgs& a, char* smem) {
   const int G = gridDim.x;
   const int g = xcd_instance_ep(blockIdx.x, G);
   constexpr bool fused = MODE == 3;
+  static_assert(PREC == 0 || fused, "the MX tiles are the fused layer's only");
   const int n1 = (MODE & 1) ? P * a.P1 : 0;
   const int n2 = (MODE & 2) ? P * a.P2 : 0;
   const bool burst = fused && a.policy == XS_POLICY_BURST, dynamic = a.claim == XS_CLAIM_DYNAMIC;

@@ -368,7 +368,10 @@ int xs_fused_ep_layer_noalloc(const xs_ep_layer* L, const xs_pacing* pacing, con
  *   a  device bf16 [M][K] (row stride lda elements), b device bf16 [N][K] (row stride ldb;
  *      the weight's output-major layout), c device bf16 [M][N] (row stride ldc).
  * Products too small to fill the GPU with 256 x 256 tiles are summed over K in parallel parts
- * (fp32, a fixed order for given M, N, K); a traced call always runs the tiles.
+ * (fp32). The order of the sum is fixed by M, N, K and the device's CU count for operands aligned
+ * to 16 bytes (c to 8) with strides of at most 2^23; others, and traced calls, always run the
+ * tiles. So a row's bits may differ between two M, between a traced and an untraced call, and from
+ * xs_gemm_scatter, which always runs the tiles.
  * Requires N % 256 == 0, K % 64 == 0, strides multiples of 8. */
 int xs_gemm(const void* a, int64_t lda, const void* b, int64_t ldb, void* c, int64_t ldc,
             int32_t M, int32_t N, int32_t K, const xs_trace* trace, void* stream);
@@ -445,7 +448,8 @@ int xs_scatter_copy(const void* c, int64_t ldc, int32_t M, int32_t N, const xs_s
  * tiles of one head and streams the head's K/V in 64-token tiles (the Q-loop), with an
  * online softmax in fp32 and bf16 probabilities for the second product. Shapes with at most
  * one such tile per CU run tiles of 32, 64 or 128 queries whose keys are split over the
- * workgroup's waves (chosen from heads and M alone).
+ * workgroup's waves (chosen from heads, M and the device's CU count alone; the split's sums are
+ * joined in fp32, and its bits differ from the unsplit order's, which a traced call runs).
  *   q, k, v  device bf16 [heads][M][head_dim]; head_dim must be 128.
  *   scale    0 = 1 / sqrt(head_dim).
  *   M        multiple of 128, at most 8,388,480 (one head's K or V rows within a 2 GiB

@@ -306,8 +306,8 @@ __global__ __launch_bounds__(kThreads, 3) void attn_kernel(Args a) {
 // flight while tile j is multiplied. What bounds the short forms is each workgroup's stream of
 // its head's whole K and V (a CU takes in about 75 B/ns), so they use the most queries per
 // workgroup that still gives every CU one.
-// Measured, 8 heads (us): M = 128 8.1 -> 5.4, 512 16.5 -> 8.8 (<1, 4, 32>); 1152 30.2 -> 16.4, 2048
-// 49 -> 25.6 (<2, 4, 32>); 4096 95 -> 71.5 (<4, 2, 64>). Three groups a phase
+// Measured, 8 heads (us): 512 16.6 -> 8.5, 1024 28.3 -> 13.6 (<1, 4, 32>); 1152 31.0 -> 16.0, 2048
+// 50.8 -> 26.4 (<2, 4, 32>); 4096 97 -> 73 (<4, 2, 64>). Three groups a phase
 // apart in lock step (K product, softmax, V product) were slower than this: 85 us at 4096.
 constexpr int kPartialBytes = 16 * 1024 + 512;   // one wave's unnormalised O' and (max, sum), in lane order
 
@@ -591,9 +591,10 @@ extern "C" int xs_attention(const xs_attn* A, int32_t mode, const xs_trace* trac
   // Waves of queries per workgroup (0: the unsplit kernel, 128 queries and three workgroups per
   // CU): the most that still leaves every CU a workgroup, from the shape alone, so that the
   // output depends neither on the grid nor on the mode. Up to one 128-query tile per CU the
-  // split forms win clearly (256 tiles: 71.5 against 95 us); from there on the unsplit kernel has
-  // its second and third workgroup (384 tiles: 181 against 188 us, 512: 265 against 275, 768: 588
-  // against 579). A trace records 128-query tiles of the unsplit kernel.
+  // split forms win clearly (256 tiles: 73 us split, 97 unsplit). From there on the unsplit kernel has
+  // its second and third workgroup and neither wins throughout (split / unsplit: 282 tiles 180 / 175, 320
+  // 155 / 151, 384 184 / 184, 512 of 8 heads 263 / 270 and of 4 heads 505 / 528, 768 579 / 570, 1024
+  // 1005 / 977); the 3 to 4 % at 512 are left. A trace records 128-query tiles of the unsplit kernel.
   const int cus = xs_host::persistent_grid(0);
   const int form = a.tr.buf || tiles > cus ? 0 : (4 * tiles <= cus ? 1 : (2 * tiles <= cus ? 2 : 4));
   if (form) tiles *= 4 / form;

@@ -411,9 +411,10 @@ __global__ __launch_bounds__(256) void layout_finalize_kernel(
 // and at a decode step's sizes nothing else. A thread per slot. Per (unit of 64 tokens of one source,
 // expert) a 64-bit lane mask in LDS gives the rank inside the unit, and, per expert, a running
 // count over the units in (source, token) order gives everything before it, which is also the row
-// order inside an expert. The fused layer's dispatch launch writes the inverse map. 8 sources of 16
-// tokens, 256 experts, with the FFN plan: chunk 7.9 + scan 10.2 us -> 9.5 us, and 3 us off the
-// dispatch, which looked up the rows' bases.
+// order inside an expert. The fused layer's dispatch launch writes the inverse map. Against the
+// kernels above, 8 sources of 16 tokens, 256 experts, with the FFN plan (kernel trace): chunk 4.9 + scan
+// 8.0 us -> 8.4, and the dispatch, which looked up the rows' bases, 12.0 -> 6.5; the bf16 layer pass
+// 501 -> 490, the tiny one 44.5 -> 41.9.
 constexpr int kSmallUnitExperts = 10240;   // units x experts whose masks and counts fit the LDS (120 KiB)
 constexpr int kSmallSlots = 4096;          // four slots per thread
 

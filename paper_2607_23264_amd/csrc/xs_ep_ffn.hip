@@ -206,8 +206,9 @@ __device__ __forceinline__ void claim_take(const EpArgs& a, Claim* cl) {
 
 // One Linear-1 tile of row p is done: its h stores went past the L2, and every wave's have
 // completed when the barrier opens, so the count itself needs no release. A release writes back
-// the L2, under every other tile on the XCD too: with one per tile the FFN of the 4096-token share
-// took 2540 us where it takes 2440, and its Linear-1 mainloops 171 us a tile instead of 161.
+// the L2, under every other tile on the XCD too. Layer passes with a release per tile and plain stores,
+// and without (us): 8 x 4096 tokens bf16 2904 / 2870, 8 x 509 MXFP8 skewed 567 / 547, 8 x 16 bf16
+// 508 / 490, 8 x 64 W4A8 208 / 197, the tiny layer 43.5 / 41.9.
 __device__ __forceinline__ void count_l1_tile(const EpArgs& a, int p) {
   wait_vm<0>();
   __syncthreads();
@@ -1153,10 +1154,11 @@ static int fused_ep_layer(const xs_ep_layer* L, const xs_pacing* pacing, const x
   const int grid = xs_host::persistent_grid(pacing ? pacing->max_producers : 0);
   const int wave_tiles = pacing && pacing->wave_tiles > 0 ? pacing->wave_tiles : grid;
   // MX tiles of more than 128 rows take twice the time of the small-tile core's: where blocks of 128
-  // rows still are one round of Linear-1 tiles, they shorten the layer (4 sources x 198 tokens of
-  // 2048, 64 experts, MXFP8, skewed: 105 -> 98 us; 1 x 1024 of 512, uniform: 64 -> 55). With a second
-  // round they do not (4 x 512 of 2048, uniform, 384 tiles: 110 -> 128). Paced and traced runs keep
-  // the 256-row order that they name.
+  // rows still are one round of Linear-1 tiles, they shorten the layer (layer passes, 256-row blocks
+  // and 128: 4 sources x 198 tokens of 2048, 64 experts, MXFP8, skewed, 252 tiles 100 / 84 us; 1 x
+  // 1024 of 512, uniform 60 / 50). A second round costs more than they save (4 x 512 of 2048, uniform,
+  // 384 tiles: 95 / 110; 264 tiles: 90 / 93; only a skewed 276 still gains, 96 / 83). Traced runs, and those that
+  // name a burst, chunk or audited order, a grid or a gap, keep 256 rows.
   const bool plain = !pacing || (pacing->policy == XS_POLICY_INTERLEAVE && !pacing->max_producers &&
                                  !pacing->gap_ns && pacing->withhold_row < 0);
   const bool halves = is_mx(L) && plain && !(trace && trace->buf && trace->count);

@@ -352,11 +352,12 @@ static xs_trace trace_or_empty(const xs_trace* t) {
 namespace {
 
 // Columns of the output tiles, and what the launch costs in rounds of 256 x 256 tiles over the CUs:
-// 192 or 128 where they leave fewer CUs idle. A 192-column tile takes up to kTile192 of the time of
-// a 256-column one, a 128-column tile up to kTile128 (0.56 to 0.82: its waves read more LDS per
-// MFMA). Measured, 256 / 192 / 128 columns (us): 1000 x 12288 x 4096 95 / 91 / 121, 4096 x 6144 x
-// 2048 109 / 92 / 99, 2048 x 4096 x 4096 78 / - / 64, 300 x 12288 x 4096 74 / 62 / 50, 8192 x 8192 x
-// 1024 125 / - / 143.
+// 192 or 128 where they leave fewer CUs idle. A narrower tile takes 0.84 to 0.96 (192) and 0.56 to 0.82
+// (128: its waves read more LDS per MFMA) of a 256-column one's time, counted here as kTile192 and
+// kTile128; since r rounds of 256 columns are at least 4 (r - 1) / 3 and 2 (r - 1) full rounds of the others,
+// the narrower tiles win only where they need no more rounds. Measured, 256 / 192 / 128 columns (us):
+// 1000 x 12288 x 4096 95 / 91 / 121, 4096 x 6144 x 2048 109 / 92 / 99, 2048 x 4096 x 4096 78 / - / 64,
+// 300 x 12288 x 4096 74 / 62 / 50, 8192 x 8192 x 1024 125 / - / 143.
 constexpr double kTile192 = 0.87, kTile128 = 0.72;
 
 double tile_rounds(int M, int N, int* columns) {

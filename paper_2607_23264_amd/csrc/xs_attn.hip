@@ -176,6 +176,10 @@ __global__ __launch_bounds__(kThreads, 3) void attn_kernel(Args a) {
     if (nkv > 1) issue_k(1);
     wait_vm0();
     asm volatile("s_barrier" ::: "memory");
+    // The K/V loop runs up to 2 % faster or slower with where its instructions fall in the 32-byte
+    // fetches. Measured at each of the eight places (3 heads x 11648 tokens, us): 330, 329, 327, 325,
+    // 322, 322, 325, 329 with 0 to 7 words past a boundary here; 8 x 16384 985, 983, 984, 975, 986, 980, 988, 983.
+    asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
     for (int j = 0; j < nkv; ++j) {
       lds_char* const ks = lds + (j & 1) * kTileBytes;
       lds_char* const vs = lds + 2 * kTileBytes;

@@ -313,6 +313,9 @@ __global__ __launch_bounds__(kThreads, 3) void attn_kernel(Args a) {
 // Measured, 8 heads (us): 512 16.6 -> 8.5, 1024 28.3 -> 13.6 (<1, 4, 32>); 1152 31.0 -> 16.0, 2048
 // 50.8 -> 26.4 (<2, 4, 32>); 4096 97 -> 73 (<4, 2, 64>). Three groups a phase
 // apart in lock step (K product, softmax, V product) were slower than this: 85 us at 4096.
+// A group's probabilities are rounded to bf16 against its own maximum, so an output differs from the
+// unsplit kernel's by 0.0024 to 0.0029 (2-norm, relative); against 64 bits it is no further off (8 x 1152: 0.00230
+// split, 0.00232 unsplit; M = 128 to 16384: 0.91 to 1.00 of the unsplit error).
 constexpr int kPartialBytes = 16 * 1024 + 512;   // one wave's unnormalised O' and (max, sum), in lane order
 
 // Two loads as load_lds16 from one write of M0: an instruction's offset counts in the buffer and in

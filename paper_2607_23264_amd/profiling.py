@@ -34,7 +34,10 @@ FFN_KERNEL_SOURCES = ("csrc/xs_ep_ffn.hip", "csrc/xs_gemm.hpp", "csrc/xs_gemm_mx
                       "csrc/xs_plan.hpp", "csrc/xs_common.hpp")
 ATTN_KERNEL_SOURCES = ("csrc/xs_attn.hip", "csrc/xs_common.hpp")
 EP_KERNEL_SOURCES = ("csrc/xs_ep.hip", "csrc/xs_plan.hpp", "csrc/xs_common.hpp")
-KERNEL_SOURCES = {"ffn": FFN_KERNEL_SOURCES, "attn": ATTN_KERNEL_SOURCES, "ep": EP_KERNEL_SOURCES}
+SPLIT_GEMM_KERNEL_SOURCES = ("csrc/xs_gemm_skinny.hpp", "csrc/xs_common.hpp")
+RING_KERNEL_SOURCES = ("csrc/xs_ring.hip", "csrc/xs_common.hpp")
+KERNEL_SOURCES = {"ffn": FFN_KERNEL_SOURCES, "attn": ATTN_KERNEL_SOURCES, "ep": EP_KERNEL_SOURCES,
+                  "split_gemm": SPLIT_GEMM_KERNEL_SOURCES, "ring": RING_KERNEL_SOURCES}
 
 
 def sources_hash(paths=FFN_KERNEL_SOURCES) -> str:

@@ -448,8 +448,9 @@ int xs_scatter_copy(const void* c, int64_t ldc, int32_t M, int32_t N, const xs_s
  * tiles of one head and streams the head's K/V in 64-token tiles (the Q-loop), with an
  * online softmax in fp32 and bf16 probabilities for the second product. Shapes with at most
  * one such tile per CU run tiles of 32, 64 or 128 queries whose keys are split over the
- * workgroup's waves (chosen from heads, M and the device's CU count alone; the split's sums are
- * joined in fp32, and its bits differ from the unsplit order's, which a traced call runs).
+ * workgroup's waves. How the keys are split follows from heads, M and the device's CU count alone,
+ * so the bits do not depend on max_producers; the split's sums are joined in fp32, and its bits
+ * differ from the unsplit order's, which a traced call runs.
  *   q, k, v  device bf16 [heads][M][head_dim]; head_dim must be 128.
  *   scale    0 = 1 / sqrt(head_dim).
  *   M        multiple of 128, at most 8,388,480 (one head's K or V rows within a 2 GiB

@@ -603,7 +603,12 @@ extern "C" int xs_attention(const xs_attn* A, int32_t mode, const xs_trace* trac
   // 155 / 151, 384 184 / 184, 512 of 8 heads 263 / 270 and of 4 heads 505 / 528, 768 579 / 570, 1024
   // 1005 / 977); the 3 to 4 % at 512 are left. A trace records 128-query tiles of the unsplit kernel.
   const int cus = xs_host::persistent_grid(0);
-  const int form = a.tr.buf || tiles > cus ? 0 : (4 * tiles <= cus ? 1 : (2 * tiles <= cus ? 2 : 4));
+  int form = a.tr.buf || tiles > cus ? 0 : (4 * tiles <= cus ? 1 : (2 * tiles <= cus ? 2 : 4));
+  // The first two forms split and join a query's keys alike, so their bits are the same: where the
+  // caller's grid is too small for a workgroup per 32 queries, 64 queries share a K/V stream. Measured,
+  // grids of 240, 64 and 8 (us, 32 / 64 queries / unsplit): 8 x 1024 25.1 / 16.1 / 28.7, 47.0 / 27.8 / 28.4, 346 /
+  // 201 / 203; 8 x 512 at 64 and 8 15.6 / 10.7 / 17.0, 106 / 67 / 60.
+  if (form == 1 && A->max_producers > 0 && A->max_producers < 4 * tiles) form = 2;
   if (form) tiles *= 4 / form;
   int grid = A->max_producers > 0 ? A->max_producers : (form ? cus : 3 * cus);
   if (grid > tiles) grid = tiles;

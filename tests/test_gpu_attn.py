@@ -112,6 +112,17 @@ def test_key_split_forms_repeat_and_lose_no_precision(heads, M):
     assert err[0] <= 1.05 * err[1]
 
 
+# shapes of 32-query tiles on a grid of a workgroup per tile, one short of that (64-query tiles from there
+# on), and far smaller ones
+@pytest.mark.parametrize("heads,M", [(1, 128), (5, 384), (8, 1024)])
+def test_key_split_bits_do_not_depend_on_the_grid(heads, M):
+    q, k, v = _inputs(heads, M, seed=95 + M)
+    want = _local(q, k, v)
+    tiles = heads * M // 32
+    for grid in (tiles, tiles - 1, tiles // 2, tiles // 2 - 1, 1):
+        assert np.array_equal(want, _local(q, k, v, max_producers=grid)), grid
+
+
 def test_keys_scoring_minus_infinity_weigh_nothing():
     # positive queries, and keys of -inf from token 40 on: whole K/V tiles (and every tile of most
     # key groups) score -inf, and the output is attention over the first 40 keys

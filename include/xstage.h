@@ -257,8 +257,8 @@ enum { XS_EXPERT_SWIGLU = 0, XS_EXPERT_IDENTITY = 1 };
  *   XS_CLAIM_DYNAMIC  producers take the next entry of a stream from a shared counter when
  *                     they finish a tile, under the same rule (a Linear-2 tile of row p is
  *                     taken only when every Linear-1 tile of rows <= p + D - 1 has been
- *                     taken; BURST: the next entry of the Expert-Wave list). Same tiles and
- *                     bytes; balances producers whose tiles differ in length.
+ *                     taken). Same tiles and bytes; balances producers whose tiles differ in
+ *                     length. BURST deals the Expert-Wave list out statically in either mode.
  * Every policy computes the same tiles and stores the same bytes; outputs are
  * bit-identical across policies. */
 enum { XS_POLICY_BURST = 0, XS_POLICY_INTERLEAVE = 1, XS_POLICY_CHUNK = 2, XS_POLICY_AUTO = 3 };

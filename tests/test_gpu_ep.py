@@ -395,7 +395,8 @@ def _records(buf, count):
     return kind, wg, tile, r
 
 
-@pytest.mark.parametrize("policy", ["interleave", "chunk", "wave"])
+# (the Expert-Wave list is dealt out statically in either claim mode)
+@pytest.mark.parametrize("policy", ["interleave", "chunk", "wave", "wave_dyn"])
 def test_device_tile_order_matches_schedule_oracle(policy):
     from paper_2607_23264_amd.layer import pacing
     X = xs()
@@ -406,7 +407,8 @@ def test_device_tile_order_matches_schedule_oracle(policy):
     G = 8
     pol = {"interleave": pacing(X.XS_POLICY_INTERLEAVE, lead=2, max_producers=G),
            "chunk": pacing(X.XS_POLICY_CHUNK, lead=1, chunk=1, max_producers=G),
-           "wave": pacing(X.XS_POLICY_BURST, max_producers=G, wave_tiles=16)}[policy]
+           "wave": pacing(X.XS_POLICY_BURST, max_producers=G, wave_tiles=16),
+           "wave_dyn": pacing(X.XS_POLICY_BURST, max_producers=G, wave_tiles=16, claim=X.XS_CLAIM_DYNAMIC)}[policy]
     buf = torch.zeros((4096, 4), dtype=torch.int64, device="cuda")
     cnt = torch.zeros((1,), dtype=torch.int32, device="cuda")
     tr = X.xs_trace(buf.data_ptr(), buf.shape[0], cnt.data_ptr())

@@ -493,13 +493,13 @@ __device__ __forceinline__ int final_row(const FinArgs& fa, int E, int s, int t,
          fa.chunk_base[(static_cast<int64_t>(s) * fa.n_chunks + t / kChunk) * E + e] + r;
 }
 
-// `parts` waves per token, each a part of its row: one for large batches (with 4096 tokens a
+// 1 << parts_log2 waves per token, each a part of its row: one for large batches (with 4096 tokens a
 // quarter row per wave is slower), up to eight for small ones, where a lone wave would issue the k
 // copies of a whole row by itself (16 tokens of 14 KiB, k = 8: 10.8 us with one). Lanes hold up to 8
 // 16-byte pieces of the row per round and store them into the k destination rows. Where the
 // waves also finish the rows (idx_all, not rows_final), one wave per token only.
 __global__ __launch_bounds__(256) void dispatch_kernel(const char* __restrict__ x, int64_t x_stride,
-                                                       int nch, int T, int parts,
+                                                       int nch, int T, int parts_log2,
                                                        const int* __restrict__ idx,
                                                        int* __restrict__ slot_row, int k,
                                                        int E, WinSet win, int* status, FinArgs fa) {
@@ -529,9 +529,10 @@ __global__ __launch_bounds__(256) void dispatch_kernel(const char* __restrict__ 
     }
     return;
   }
-  const int wv = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int t = wv / parts, part = wv - t * parts;
-  const int per = (nch + parts - 1) / parts, c_begin = part * per, c_end = min(nch, c_begin + per);
+  // uniform, as what follows from it: a part's bounds held per lane made every piece's test a masked one
+  const int wv = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+  const int t = wv >> parts_log2, parts = 1 << parts_log2;
+  const int per = (nch + parts - 1) >> parts_log2, c_begin = (wv & (parts - 1)) * per, c_end = min(nch, c_begin + per);
   // lane j < k resolves destination j; broadcast below with readlane
   char* my_dst = nullptr;
   if (t < T && lane < k) {
@@ -592,19 +593,17 @@ __global__ __launch_bounds__(256) void dispatch_kernel(const char* __restrict__ 
 __global__ __launch_bounds__(256) void combine_reduce_kernel(const char* __restrict__ cbuf,
                                                              int64_t cstride,
                                                              const float* __restrict__ w, int T,
-                                                             int k, int H, int parts,
+                                                             int k, int H, int parts_log2,
                                                              uint16_t* __restrict__ out) {
   const int lane = threadIdx.x & 63;
-  // `parts` waves per token, each over a part of the row's 16-byte pieces: four for large batches
-  // (one wave per token left 16 waves per CU at T = 4096, too few loads in flight to stream HBM),
-  // for small ones as many as leave each a single pass
+  // 1 << parts_log2 waves per token, each over a part of the row's 16-byte pieces (combine_reduce)
   const int wv = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int t = wv / parts;
+  const int t = wv >> parts_log2, parts = 1 << parts_log2;
   if (t >= T) return;
   const float wl = lane < k ? w[static_cast<int64_t>(t) * k + lane] : 0.f;
   const int nch = H >> 3;
-  const int per = (nch + parts - 1) / parts;
-  const int c_begin = (wv - t * parts) * per;
+  const int per = (nch + parts - 1) >> parts_log2;
+  const int c_begin = (wv & (parts - 1)) * per;
   const int c_end = min(nch, c_begin + per);
   u32x4* dst = reinterpret_cast<u32x4*>(out + static_cast<int64_t>(t) * H);
   const char* rows = cbuf + static_cast<int64_t>(t) * k * cstride;
@@ -792,14 +791,17 @@ int dispatch_layout(const int32_t* topk_idx, int32_t n_src, int32_t T, int32_t k
 // their slots.
 // With fin (the fused layer), the same launch finishes the layout (FinArgs) and, when the
 // windows have flags, signals them from its last dispatch block.
+// 0 for n < 2.
+static int floor_log2(int n) { return n < 2 ? 0 : 31 - __builtin_clz(static_cast<unsigned>(n)); }
+
 int dispatch_rows(const void* x, int64_t x_stride, int32_t row_bytes, int32_t T,
                   const int32_t* topk_idx, const int32_t* slot_row, int32_t k, int32_t E,
                   const WinSet& ws, int32_t* dev_status, hipStream_t st, const FinArgs* fin) {
   FinArgs fa{};
   if (fin) fa = *fin;
   const int nch = row_bytes / 16;
-  const int parts = (fa.idx_all && !fa.rows_final) || T < 1 ? 1 : std::max(1, std::min({8, 1024 / T, nch / 64}));
-  const int nd = static_cast<int>((static_cast<int64_t>(T) * parts + 3) / 4);
+  const int parts_log2 = (fa.idx_all && !fa.rows_final) || T < 1 ? 0 : floor_log2(std::min({8, 1024 / T, nch / 64}));
+  const int nd = static_cast<int>(((static_cast<int64_t>(T) << parts_log2) + 3) / 4);
   int nf = 0;
   if (fin) {
     fa.n_disp_blocks = nd;
@@ -811,7 +813,7 @@ int dispatch_rows(const void* x, int64_t x_stride, int32_t row_bytes, int32_t T,
   }
   if (nd + nf > 0) {
     hipLaunchKernelGGL(dispatch_kernel, dim3(nd + nf), dim3(256), 0, st, static_cast<const char*>(x),
-                       x_stride, nch, T, parts, topk_idx, const_cast<int32_t*>(slot_row), k, E, ws,
+                       x_stride, nch, T, parts_log2, topk_idx, const_cast<int32_t*>(slot_row), k, E, ws,
                        dev_status, fa);
     if (launch_status()) return XS_EHIP;
   }
@@ -827,10 +829,23 @@ int dispatch(const void* x, int32_t T, int32_t H, const int32_t* topk_idx, const
 int combine_reduce(const void* cbuf, int64_t cstride, const float* w, int32_t T, int32_t k,
                    int32_t H, void* out, hipStream_t st) {
   if (T == 0) return XS_OK;
-  const int parts = T >= 1024 ? 4 : std::max(1, std::min(16, (H / 8 + 127) / 128));
-  const int64_t blocks = (static_cast<int64_t>(T) * parts + 3) / 4;
+  // Waves per token: four (one left 16 waves per CU at T = 4096, too few loads in flight to stream HBM).
+  // In small batches a long row's parts are one pass of 128 pieces each, short rows get no more than 2048
+  // waves in all, and a row that gives each lane of one wave a piece (or few rows with less) is not
+  // divided. Measured, k = 8, 1 / 2 / 4 / 8 waves (us): T = 64, H = 7168 12.6 / 7.9 / 5.0 / 3.5, 2048 4.9 / 3.4 /
+  // 3.3 / 3.3, 512 3.2 / 3.2 / 3.4 / 5.3; T = 512, 7168 21.9 / 14.2 / 11.7 / 11.2, 2048 7.2 / 4.6 / 3.7 / 5.5, 512
+  // 3.3 / 3.4 / 3.5 / 6.8; T = 1000, k = 6, 2048 5.3 / 4.3 / 5.7 / 7.6. A power of two: the division of the
+  // wave's number by the parts took 0.2 us of a call.
+  const int nch = H / 8;
+  int parts_log2 = 2;
+  if (T < 1024) {
+    parts_log2 = std::max(2, std::min(4, floor_log2(2 * ((nch + 127) / 128) - 1)));
+    if (nch <= 256) parts_log2 = std::min(parts_log2, floor_log2(2048 / T));
+    if (nch <= 64 && (nch > 32 || T <= 256)) parts_log2 = 0;
+  }
+  const int64_t blocks = ((static_cast<int64_t>(T) << parts_log2) + 3) / 4;
   hipLaunchKernelGGL(combine_reduce_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st,
-                     static_cast<const char*>(cbuf), cstride, w, T, k, H, parts,
+                     static_cast<const char*>(cbuf), cstride, w, T, k, H, parts_log2,
                      static_cast<uint16_t*>(out));
   return launch_status();
 }

@@ -597,7 +597,7 @@ __global__ __launch_bounds__(256) void combine_reduce_kernel(const char* __restr
                                                              uint16_t* __restrict__ out) {
   const int lane = threadIdx.x & 63;
   // 1 << parts_log2 waves per token, each over a part of the row's 16-byte pieces (combine_reduce)
-  const int wv = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int wv = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
   const int t = wv >> parts_log2, parts = 1 << parts_log2;
   if (t >= T) return;
   const float wl = lane < k ? w[static_cast<int64_t>(t) * k + lane] : 0.f;
@@ -608,10 +608,11 @@ __global__ __launch_bounds__(256) void combine_reduce_kernel(const char* __restr
   u32x4* dst = reinterpret_cast<u32x4*>(out + static_cast<int64_t>(t) * H);
   const char* rows = cbuf + static_cast<int64_t>(t) * k * cstride;
   // two 16-byte pieces per lane per pass, the slots' loads issued in blocks of eight before
-  // any sum (a loop over the runtime k kept only two loads in flight)
-  for (int c0 = c_begin + lane; c0 < c_end; c0 += 128) {
-    const int c1 = c0 + 64;
-    const bool two = c1 < c_end;
+  // any sum (a loop over the runtime k kept only two loads in flight). Every lane makes every pass: those
+  // without a piece still hold their slot's weight
+  for (int c = c_begin; c < c_end; c += 128) {
+    const int c0 = c + lane, c1 = c0 + 64;
+    const bool one = c0 < c_end, two = c1 < c_end;
     float acc[2][8];
 #pragma unroll
     for (int h = 0; h < 2; ++h)
@@ -624,14 +625,14 @@ __global__ __launch_bounds__(256) void combine_reduce_kernel(const char* __restr
         p0[jj] = p1[jj] = u32x4{0u, 0u, 0u, 0u};
         if (j0 + jj < k) {
           const u32x4* r = reinterpret_cast<const u32x4*>(rows + static_cast<int64_t>(j0 + jj) * cstride);
-          p0[jj] = __builtin_nontemporal_load(r + c0);   // each combine row is read once
+          if (one) p0[jj] = __builtin_nontemporal_load(r + c0);   // each combine row is read once
           if (two) p1[jj] = __builtin_nontemporal_load(r + c1);
         }
       }
 #pragma unroll
       for (int jj = 0; jj < 8; ++jj) {
         if (j0 + jj >= k) break;
-        const float wj = __shfl(wl, j0 + jj);
+        const float wj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wl), j0 + jj));
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           acc[0][2 * q] += wj * bf_lo(p0[jj][q]);
@@ -647,7 +648,7 @@ __global__ __launch_bounds__(256) void combine_reduce_kernel(const char* __restr
       o0[q] = pack_bf16x2(acc[0][2 * q], acc[0][2 * q + 1]);
       o1[q] = pack_bf16x2(acc[1][2 * q], acc[1][2 * q + 1]);
     }
-    dst[c0] = o0;
+    if (one) dst[c0] = o0;
     if (two) dst[c1] = o1;
   }
 }
@@ -829,19 +830,18 @@ int dispatch(const void* x, int32_t T, int32_t H, const int32_t* topk_idx, const
 int combine_reduce(const void* cbuf, int64_t cstride, const float* w, int32_t T, int32_t k,
                    int32_t H, void* out, hipStream_t st) {
   if (T == 0) return XS_OK;
-  // Waves per token: four (one left 16 waves per CU at T = 4096, too few loads in flight to stream HBM).
-  // In small batches a long row's parts are one pass of 128 pieces each, short rows get no more than 2048
-  // waves in all, and a row that gives each lane of one wave a piece (or few rows with less) is not
-  // divided. Measured, k = 8, 1 / 2 / 4 / 8 waves (us): T = 64, H = 7168 12.6 / 7.9 / 5.0 / 3.5, 2048 4.9 / 3.4 /
-  // 3.3 / 3.3, 512 3.2 / 3.2 / 3.4 / 5.3; T = 512, 7168 21.9 / 14.2 / 11.7 / 11.2, 2048 7.2 / 4.6 / 3.7 / 5.5, 512
-  // 3.3 / 3.4 / 3.5 / 6.8; T = 1000, k = 6, 2048 5.3 / 4.3 / 5.7 / 7.6. A power of two: the division of the
-  // wave's number by the parts took 0.2 us of a call.
+  // Waves per token: four (one left 16 waves per CU at T = 4096, too few loads in flight to stream HBM), a
+  // long row's as many as make each part one pass of 128 pieces; one where that gives each lane a piece at
+  // most, and in small batches no more than 2048 for all the short rows. Measured, 1 / 2 / 4 / 8 waves (us):
+  // k = 8, T = 64, H = 7168 12.7 / 7.9 / 4.9 / 3.4, 2048 4.8 / 3.3 / 3.3 / 3.3, 512 3.2 / 3.2 / 3.2 / 3.2; T = 512, 7168
+  // 20.7 / 14.0 / 11.3 / 10.1, 2048 6.5 / 4.3 / 3.8 / 5.0, 512 3.3 / 3.4 / 3.6 / 4.7; T = 4096, 7168 97 / 95 / 91 / 87, 2048
+  // 28.7 / 25.5 / 24.2 / 27.9, 512 5.9 / 8.2 / 13.0 / 22.3; k = 6, T = 1000, 2048 5.3 / 4.4 / 5.1 / 7.1. A power of two:
+  // the division of the wave's number by the parts took 0.2 us of a call.
   const int nch = H / 8;
-  int parts_log2 = 2;
-  if (T < 1024) {
+  int parts_log2 = 0;
+  if (nch > 64) {
     parts_log2 = std::max(2, std::min(4, floor_log2(2 * ((nch + 127) / 128) - 1)));
-    if (nch <= 256) parts_log2 = std::min(parts_log2, floor_log2(2048 / T));
-    if (nch <= 64 && (nch > 32 || T <= 256)) parts_log2 = 0;
+    if (nch <= 256 && T < 1024) parts_log2 = std::min(parts_log2, floor_log2(2048 / T));
   }
   const int64_t blocks = ((static_cast<int64_t>(T) << parts_log2) + 3) / 4;
   hipLaunchKernelGGL(combine_reduce_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st,

@@ -217,6 +217,47 @@ def test_dispatch_capacity_overflow_skips_rows():
     assert np.array_equal(host_bits(win), ref)
 
 
+# one to eight waves per token, with parts that do not divide the row
+@pytest.mark.parametrize("T,H", [(1, 7176), (5, 8), (127, 4104), (129, 4104), (256, 1032), (511, 2056), (513, 2056), (1025, 1024)])
+def test_dispatch_row_parts_bitexact(T, H):
+    X = xs()
+    k, E, W = 3, 16, 4
+    idx = _idx_random(1, T, k, E, seed=T)[0]
+    lay = oep.dispatch_layout(idx[None], E, W, cap=T * k)
+    cap = int(lay["dest_counts"].max())
+    x = synth.normal_bf16(0, 1, (T, H))
+    win = torch.full((W, cap, H), -1, dtype=torch.int16, device="cuda")
+    wins = X.windows([X.window(win[d]) for d in range(W)])
+    st = torch.zeros((1,), dtype=torch.int32, device="cuda")
+    dx, ti, sr = dev_bits(x), torch.from_numpy(idx).cuda(), torch.from_numpy(lay["slot_row"][0]).cuda()
+    X.check(X.xs_dispatch(dx.data_ptr(), T, H, ti.data_ptr(), sr.data_ptr(), k, E, wins, W, st.data_ptr(),
+                          torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    assert int(st.item()) == 0
+    ref, _ = oep.dispatch(x[None], idx[None], lay["slot_row"], E, W, cap)
+    assert np.array_equal(host_bits(win), ref)
+
+
+# the edges of the rule for the waves per token: one piece per lane, one pass per part, the bound on the
+# waves of short rows; and passes of fewer pieces than slots, whose weights lie in lanes that have none
+@pytest.mark.parametrize("T,k,H", [(3, 32, 264), (300, 3, 512), (300, 3, 520), (512, 2, 2048), (513, 2, 2048), (1023, 2, 2048),
+                                   (1024, 2, 2048), (700, 2, 2056), (9, 9, 4104), (3, 2, 8200), (2, 2, 16392), (1024, 8, 4160),
+                                   (1024, 2, 264), (300, 12, 64), (7, 4, 8)])
+def test_combine_reduce_row_parts_match_oracle(T, k, H):
+    X = xs()
+    c = synth.normal_bf16(0, 9, (T * k, H))
+    w = np.random.default_rng(T).random((T, k)).astype(np.float32)
+    out = torch.full((T + 1, H), -1, dtype=torch.int16, device="cuda")
+    ct, wt = dev_bits(c), torch.from_numpy(w).cuda()
+    X.check(X.xs_combine_reduce(ct.data_ptr(), H * 2, wt.data_ptr(), T, k, H, out.data_ptr(),
+                                torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    ref64, _ = oep.combine_reduce(c, w)
+    got = host_bits(out)
+    assert_close(got[:T], ref64, f"combine T={T} k={k} H={H}")
+    assert (got[T] == 0xFFFF).all()
+
+
 def test_combine_reduce_matches_oracle():
     X = xs()
     g = np.random.default_rng(4)
